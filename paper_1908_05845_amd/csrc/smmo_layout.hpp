@@ -52,8 +52,8 @@ enum : uint32_t {
 // control word indices (uint32 units; 64-bit counters take two words)
 enum : uint32_t {
     CTRL_ERR = 0,
-    CTRL_GCOUNT = 8,      // gather: running output count
-    CTRL_GDONE = 9,       // gather: finished wavefronts
+    CTRL_GATHER = 8,      // u64: gather: running output count (bits 0-31) and work-groups that
+                          // have counted all their objects (32-63); zero between gathers
     CTRL_RPACK = 16,      // [class] u64 (words 16 + 2 class): an enumeration's running
                           // dense count (bits 0-24), sparse count (25-49) and
                           // finished work-groups (50-63); zero between enumerations
