@@ -126,27 +126,15 @@ __device__ __forceinline__ bool st_valid(const HeapView &h, uint32_t handle)
 }
 
 // Deletes the objects named by `handle` on the lanes with want, of whatever
-// class each block holds (the block's type id).  Converged call.  Lanes
-// naming slots of one block are released together, one block per round.
+// class each block holds (the block's type id).  Converged call.
 __device__ __forceinline__ void wave_delete_any(const HeapView &h, uint32_t handle, bool want)
 {
-    const uint32_t lane = lane_id();
-    uint64_t pending = __ballot(want);
-    while (pending) {
-        const uint32_t leader = (uint32_t)(__ffsll((unsigned long long)pending) - 1);
-        const uint32_t b = (uint32_t)__shfl((int)(handle >> 6), (int)leader);
-        const bool mine = ((pending >> lane) & 1) && (handle >> 6) == b;
-        const uint64_t slots = wave_or64(mine ? 1ull << (handle & 63) : 0ull);
-        pending &= ~__ballot(mine);
-        OpQueue q;
-        q.reset();
-        if (lane == leader) {
-            const uint32_t cls = h.type[b];
-            if (cls < h.nclasses) release_slots(h, cls, b, slots, q);
-            else raise_error(h, ERR_BADHANDLE);
-        }
-        run_ops_wave(h, q);
-    }
+    wave_release_handles(h, handle, want, [&](uint32_t b) {
+        const uint32_t cls = h.type[b];
+        if (cls < h.nclasses) return cls;
+        raise_error(h, ERR_BADHANDLE);
+        return kNull;
+    });
 }
 
 // Node::remove_spring for the spring in slot q of node `node`; returns true
