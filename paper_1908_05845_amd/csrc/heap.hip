@@ -780,6 +780,35 @@ LaunchShape method_shape(const smmo_heap *h, uint32_t cls, uint32_t def_group)
     return ls;
 }
 
+void *class_workspace(smmo_heap *h, uint32_t cls, size_t bytes, hipStream_t st)
+{
+    smmo_heap::Workspace *&cur = h->work[cls];
+    if (cur && cur->bytes >= bytes) return cur->p;
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &cap) != hipSuccess) {
+        (void)hipGetLastError();
+        return nullptr;
+    }
+    if (cap != hipStreamCaptureStatusNone) return nullptr;
+    smmo_heap::Workspace *w = new (std::nothrow) smmo_heap::Workspace();
+    if (!w) return nullptr;
+    // room to grow by half, so that a growing class does not take one each time
+    w->bytes = cur ? bytes + bytes / 2 : bytes;
+    if (h->owner.alloc) {
+        w->p = h->owner.alloc(w->bytes, h->owner.ctx);
+    } else if (hipMalloc(&w->p, w->bytes) != hipSuccess) {
+        (void)hipGetLastError();
+        w->p = nullptr;
+    }
+    if (!w->p) {
+        delete w;
+        return nullptr;
+    }
+    w->older = cur;
+    cur = w;
+    return w->p;
+}
+
 uint32_t class_family(const smmo_schema *s, uint32_t cls)
 {
     uint32_t fam = 0;
@@ -1070,6 +1099,14 @@ smmo_status smmo_heap_free(smmo_heap *h)
 {
     if (!h) return SMMO_OK;
     if (h->base) (void)hipStreamSynchronize(h->last);
+    for (smmo_heap::Workspace *&w : h->work)
+        while (w) {
+            smmo_heap::Workspace *const older = w->older;
+            if (h->owner.release) h->owner.release(w->p, w->bytes, h->owner.ctx);
+            else (void)hipFree(w->p);
+            delete w;
+            w = older;
+        }
     if (h->host_ctrl) (void)hipHostFree(h->host_ctrl);
     if (h->base && h->owner.release) h->owner.release(h->base, h->bytes, h->owner.ctx);
     h->base = nullptr;

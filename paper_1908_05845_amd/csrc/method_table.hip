@@ -13,14 +13,16 @@ smmo_status launch_gol_cell_count(smmo_heap *h, uint32_t cls, const void *args, 
 smmo_status launch_gol_alive_death(smmo_heap *h, uint32_t cls, const void *args, hipStream_t st);
 smmo_status launch_gol_cell_birth(smmo_heap *h, uint32_t cls, const void *args, hipStream_t st);
 smmo_status launch_gol_generation(smmo_heap *h, uint32_t cls, const void *args, hipStream_t st);
-smmo_status launch_nbody_force(smmo_heap *h, uint32_t cls, const void *args, hipStream_t st);
-smmo_status launch_nbody_update(smmo_heap *h, uint32_t cls, const void *args, hipStream_t st);
 smmo_status launch_test_axpy(smmo_heap *h, uint32_t cls, const void *args, hipStream_t st);
 smmo_status launch_test_destroy_if(smmo_heap *h, uint32_t cls, const void *args, hipStream_t st);
 smmo_status launch_test_spawn(smmo_heap *h, uint32_t cls, const void *args, hipStream_t st);
 smmo_status launch_test_transmute(smmo_heap *h, uint32_t cls, const void *args, hipStream_t st);
 smmo_status launch_ls_alloc(smmo_heap *h, uint32_t cls, const void *args, hipStream_t st);
 smmo_status launch_ls_free(smmo_heap *h, uint32_t cls, const void *args, hipStream_t st);
+
+// launchers defined in nbody.hip
+smmo_status launch_nbody_force(smmo_heap *h, uint32_t cls, const void *args, hipStream_t st);
+smmo_status launch_nbody_update(smmo_heap *h, uint32_t cls, const void *args, hipStream_t st);
 
 // launchers defined in spring.hip
 smmo_status launch_spring_force(smmo_heap *h, uint32_t cls, const void *args, hipStream_t st);

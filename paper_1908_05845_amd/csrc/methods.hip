@@ -1,6 +1,6 @@
-// Methods that smmo_parallel_do() can run: Game of Life, n-body, the test
-// methods and the allocator microbenchmark (argument structs and field
-// contracts in include/smmo_methods.h; the spring-mass methods are in
+// Methods that smmo_parallel_do() can run: Game of Life, the test methods and
+// the allocator microbenchmark (argument structs and field contracts in
+// include/smmo_methods.h; n-body is in nbody.hip, the spring-mass methods in
 // spring.hip, wa-tor in wator.hip, the adjoint in adjoint.hip).
 //
 // Every method kernel walks the class's block list R (built by the
@@ -318,153 +318,6 @@ smmo_status run_gol_generation(smmo_heap *h, uint32_t cls, const void *args, hip
     return SMMO_OK;
 }
 
-// ============================================================= n-body =====
-struct NbodyK {
-    uint32_t cls;
-    uint32_t o_x, o_y, o_vx, o_vy, o_fx, o_fy, o_m;
-    float G, eps2, dt;
-};
-
-// Body::compute_force with device_do over all bodies (Ch.7 "nbody").  A
-// work-group owns one block of 64 bodies i (one per lane in every wave);
-// its four wavefronts split the other bodies j block-wise (wave w takes
-// every fourth block of R), stage each j-block in LDS and read it back as
-// broadcasts.  Each wave sums one j-block (64 terms) into a fresh float32
-// partial and adds the partial to its running sum with Kahan compensation;
-// the four running sums are combined in wave order.  The thesis leaves this
-// shared-memory tiling as future work (its "Further Optimizations").
-template <bool kGuard>
-__global__ __launch_bounds__(256) void k_nbody_force(HeapView h, NbodyK p)
-{
-    __shared__ float4 tile[4][64];
-    __shared__ float2 red[4][64];
-    if (heap_failed(h)) return;
-    const BlockList L = block_list(h, p.cls);
-    const uint32_t lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    for (uint32_t ib = xcd_logical_wg(); ib < L.r; ib += gridDim.x) {
-        const uint32_t bid = L.at(ib);
-        if (ald32(h.type + bid) != p.cls) continue;     // same for the whole work-group
-        const uint64_t bmi = ald(h.alloc_bm + bid);
-        const float xi = farr<float>(h, bid, p.o_x)[lane];
-        const float yi = farr<float>(h, bid, p.o_y)[lane];
-        float ax = 0.f, ay = 0.f, cx = 0.f, cy = 0.f;
-        for (uint32_t j0 = 0; j0 < L.r; j0 += 4) {
-            const uint32_t jt = j0 + w;
-            if (jt >= L.r) break;                        // wave-uniform
-            const uint32_t jb = __builtin_amdgcn_readfirstlane(L.at(jt));
-            if (__builtin_amdgcn_readfirstlane(ald32(h.type + jb)) != p.cls) continue;
-            const uint64_t bmj = uniform64(ald(h.alloc_bm + jb));
-            float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-            if ((bmj >> lane) & 1)
-                v = make_float4(farr<float>(h, jb, p.o_x)[lane], farr<float>(h, jb, p.o_y)[lane],
-                                farr<float>(h, jb, p.o_m)[lane], 0.f);
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            tile[w][lane] = v;
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-            float tx = 0.f, ty = 0.f;
-#pragma unroll 8
-            for (int j = 0; j < 64; ++j) {
-                const float4 q = tile[w][j];
-                const float dx = q.x - xi, dy = q.y - yi;
-                const float r2 = fmaf(dx, dx, fmaf(dy, dy, p.eps2));
-                float inv = __frsqrt_rn(r2);
-                if (kGuard) inv = r2 > 0.f ? inv : 0.f;
-                const float sc = q.z * inv * (inv * inv);
-                tx = fmaf(dx, sc, tx);
-                ty = fmaf(dy, sc, ty);
-            }
-            float yx = tx - cx, t = ax + yx;
-            cx = (t - ax) - yx;
-            ax = t;
-            float yy = ty - cy;
-            t = ay + yy;
-            cy = (t - ay) - yy;
-            ay = t;
-        }
-        red[w][lane] = make_float2(ax, ay);
-        __syncthreads();
-        if (w == 0 && ((bmi >> lane) & 1)) {
-            float sx = 0.f, sy = 0.f;
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                sx += red[k][lane].x;
-                sy += red[k][lane].y;
-            }
-            const float gm = p.G * farr<float>(h, bid, p.o_m)[lane];
-            farr<float>(h, bid, p.o_fx)[lane] = gm * sx;
-            farr<float>(h, bid, p.o_fy)[lane] = gm * sy;
-        }
-        __syncthreads();
-    }
-}
-
-// Body::update - v += f / m dt; x += v dt (velocity first)
-__global__ __launch_bounds__(1024) void k_nbody_update(HeapView h, NbodyK p)
-{
-    for_each_block(h, p.cls, false, [&](uint32_t bid, uint64_t bm) {
-        const uint32_t s = lane_id();
-        if (!((bm >> s) & 1)) return;
-        const float m = farr<float>(h, bid, p.o_m)[s];
-        float vx = farr<float>(h, bid, p.o_vx)[s], vy = farr<float>(h, bid, p.o_vy)[s];
-        vx += farr<float>(h, bid, p.o_fx)[s] / m * p.dt;
-        vy += farr<float>(h, bid, p.o_fy)[s] / m * p.dt;
-        farr<float>(h, bid, p.o_vx)[s] = vx;
-        farr<float>(h, bid, p.o_vy)[s] = vy;
-        farr<float>(h, bid, p.o_x)[s] += vx * p.dt;
-        farr<float>(h, bid, p.o_y)[s] += vy * p.dt;
-    });
-}
-
-smmo_status bind_nbody(smmo_heap *h, uint32_t cls, const smmo_nbody_args &a, NbodyK &k)
-{
-    if (!(a.eps >= 0.f) || !(a.dt == a.dt) || !(a.G == a.G)) return fail(SMMO_EINVAL, "nbody: bad parameters");
-    k.cls = cls;
-    BIND(cls, "pos_x", SMMO_F32, 1, &k.o_x, nullptr);
-    BIND(cls, "pos_y", SMMO_F32, 1, &k.o_y, nullptr);
-    BIND(cls, "vel_x", SMMO_F32, 1, &k.o_vx, nullptr);
-    BIND(cls, "vel_y", SMMO_F32, 1, &k.o_vy, nullptr);
-    BIND(cls, "force_x", SMMO_F32, 1, &k.o_fx, nullptr);
-    BIND(cls, "force_y", SMMO_F32, 1, &k.o_fy, nullptr);
-    BIND(cls, "mass", SMMO_F32, 1, &k.o_m, nullptr);
-    k.G = a.G;
-    k.eps2 = a.eps * a.eps;
-    k.dt = a.dt;
-    return SMMO_OK;
-}
-
-smmo_status nbody_force_launch(smmo_heap *h, uint32_t cls, const void *args, hipStream_t st)
-{
-    smmo_nbody_args a;
-    memcpy(&a, args, sizeof a);
-    NbodyK k;
-    smmo_status s = cached_bind(h, (const void *)&nbody_force_launch, cls, a, k,
-                                [&] { return bind_nbody(h, cls, a, k); });
-    if (s) return s;
-    if ((s = ensure_enumerated(h, cls, false, st))) return s;
-    const uint32_t grid = (uint32_t)std::min<uint64_t>(std::max<uint64_t>(1, h->ub_blocks[cls]), 8192);
-    if (k.eps2 > 0.f)
-        hipLaunchKernelGGL(k_nbody_force<false>, dim3(grid), dim3(256), 0, st, h->v, k);
-    else
-        hipLaunchKernelGGL(k_nbody_force<true>, dim3(grid), dim3(256), 0, st, h->v, k);
-    return launched("k_nbody_force");
-}
-
-smmo_status nbody_update_launch(smmo_heap *h, uint32_t cls, const void *args, hipStream_t st)
-{
-    smmo_nbody_args a;
-    memcpy(&a, args, sizeof a);
-    NbodyK k;
-    smmo_status s = cached_bind(h, (const void *)&nbody_update_launch, cls, a, k,
-                                [&] { return bind_nbody(h, cls, a, k); });
-    if (s) return s;
-    if ((s = ensure_enumerated(h, cls, false, st))) return s;
-    hipLaunchKernelGGL(k_nbody_update, method_shape(h, cls).grid, method_shape(h, cls).block, 0, st, h->v, k);
-    return launched("k_nbody_update");
-}
-
 // ======================================================= test methods =====
 struct AxpyK {
     uint32_t cls, o_x;
@@ -698,8 +551,6 @@ smmo_status launch_gol_cell_count(smmo_heap *h, uint32_t c, const void *a, hipSt
 smmo_status launch_gol_alive_death(smmo_heap *h, uint32_t c, const void *a, hipStream_t s) { return launch_gol<1>(h, c, a, s); }
 smmo_status launch_gol_cell_birth(smmo_heap *h, uint32_t c, const void *a, hipStream_t s) { return launch_gol<2>(h, c, a, s); }
 smmo_status launch_gol_generation(smmo_heap *h, uint32_t c, const void *a, hipStream_t s) { return run_gol_generation(h, c, a, s); }
-smmo_status launch_nbody_force(smmo_heap *h, uint32_t c, const void *a, hipStream_t s) { return nbody_force_launch(h, c, a, s); }
-smmo_status launch_nbody_update(smmo_heap *h, uint32_t c, const void *a, hipStream_t s) { return nbody_update_launch(h, c, a, s); }
 smmo_status launch_test_axpy(smmo_heap *h, uint32_t c, const void *a, hipStream_t s) { return launch_axpy(h, c, a, s); }
 smmo_status launch_test_destroy_if(smmo_heap *h, uint32_t c, const void *a, hipStream_t s) { return launch_destroy_if(h, c, a, s); }
 smmo_status launch_test_spawn(smmo_heap *h, uint32_t c, const void *a, hipStream_t s) { return launch_spawn(h, c, a, s); }

@@ -87,6 +87,15 @@ struct smmo_heap {
     uint32_t launch_waves[64][SMMO_MAX_CLASSES] = {};
     uint8_t launch_group[64][SMMO_MAX_CLASSES] = {};
     uint32_t cur_method = 0xFFFFFFFFu;     // method being launched by smmo_parallel_do
+    // device workspaces of methods over a class (class_workspace): the one in
+    // use per class, and all that were taken, which graphs may refer to and
+    // smmo_heap_free gives back
+    struct Workspace {
+        void *p = nullptr;
+        size_t bytes = 0;
+        Workspace *older = nullptr;
+    };
+    Workspace *work[SMMO_MAX_CLASSES] = {};
     uint64_t defrag_nonce = 0;             // marks the source blocks of a defragmentation pass
 };
 
@@ -135,6 +144,13 @@ bool packing_wanted(const smmo_heap *h, uint32_t cls, const LaunchShape &ls);
 // bookkeeping after a launch that creates objects of class cls (in_method:
 // a method's device allocation, not a host-side bulk creation)
 void note_allocation(smmo_heap *h, uint32_t cls, uint64_t max_new_objects, bool in_method = true);
+
+// A device workspace of at least `bytes` for a method over class cls, kept by
+// the heap (its contents do not survive a launch; classes have their own, so
+// launches over different classes may overlap).  NULL when there is none to be
+// had: the method then takes a path without one.  A stream that is being
+// captured gets only a workspace that is there already.
+void *class_workspace(smmo_heap *h, uint32_t cls, size_t bytes, hipStream_t st);
 
 struct MethodEntry {
     const char *name;
