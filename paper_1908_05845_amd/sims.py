@@ -63,6 +63,18 @@ def _np(t):
     return t.detach().cpu().numpy()
 
 
+def _repeat(heap, args, launches, n, stream):
+    """n times the do-alls `launches` = [(class, method), ...] with one
+    argument struct, on one stream, looked up once: a launch then costs one
+    foreign call, about 3 us where smmo_parallel_do takes 7, and the kernels
+    of a small simulation last 4 to 8."""
+    bound = [smmo.BoundLaunch(heap, cls, method, args) for cls, method in launches]
+    st = smmo._stream(stream)
+    for _ in range(n):
+        for launch in bound:
+            launch(st)
+
+
 class GolSim:
     """Game of Life in SMMO form on a W x H torus (Cell + Alive classes).
 
@@ -104,14 +116,10 @@ class GolSim:
     def step(self, n: int = 1, stream=None):
         h, c, a = self.heap.h, self.heap.cls["Cell"], self.heap.cls["Alive"]
         if self.fused:
-            for _ in range(n):
-                smmo.smmo_parallel_do(h, c, self.m_gen, self.args, stream)
+            _repeat(h, self.args, [(c, self.m_gen)], n, stream)
             return
         if not self.concurrent:
-            for _ in range(n):
-                smmo.smmo_parallel_do(h, c, self.m_count, self.args, stream)
-                smmo.smmo_parallel_do(h, a, self.m_death, self.args, stream)
-                smmo.smmo_parallel_do(h, c, self.m_birth, self.args, stream)
+            _repeat(h, self.args, [(c, self.m_count), (a, self.m_death), (c, self.m_birth)], n, stream)
             return
         import torch
 
@@ -205,10 +213,8 @@ class SpringPiSim:
                                   self.args)
 
     def step(self, n: int = 1, stream=None):
-        h, cs, cn = self.heap.h, self.heap.cls["Spring"], self.heap.cls["Node"]
-        for _ in range(n):
-            smmo.smmo_parallel_do(h, cs, self.m_force, self.args, stream)
-            smmo.smmo_parallel_do(h, cn, self.m_node, self.args, stream)
+        cs, cn = self.heap.cls["Spring"], self.heap.cls["Node"]
+        _repeat(self.heap.h, self.args, [(cs, self.m_force), (cn, self.m_node)], n, stream)
 
     def read(self) -> dict:
         """Node arrays by id; adjacency (N, D) as spring ids (-1 empty, -2 a
@@ -279,11 +285,8 @@ class GenerationSim:
         self.m_update = smmo.smmo_method_id("generation.alive_update")
 
     def step(self, n: int = 1, stream=None):
-        h, c, a = self.heap.h, self.heap.cls["Cell"], self.heap.cls["Alive"]
-        for _ in range(n):
-            smmo.smmo_parallel_do(h, c, self.m_count, self.args, stream)
-            smmo.smmo_parallel_do(h, c, self.m_birth, self.args, stream)
-            smmo.smmo_parallel_do(h, a, self.m_update, self.args, stream)
+        c, a = self.heap.cls["Cell"], self.heap.cls["Alive"]
+        _repeat(self.heap.h, self.args, [(c, self.m_count), (c, self.m_birth), (a, self.m_update)], n, stream)
 
     def read(self):
         """(state u8[W*H], left i32[W*H], number of Alive objects); raises if
@@ -332,9 +335,7 @@ class NbodySim:
         smmo.smmo_parallel_do(self.heap.h, self.cls, self.m_update, self.args, stream)
 
     def step(self, n: int = 1, stream=None):
-        for _ in range(n):
-            self.force(stream)
-            self.update(stream)
+        _repeat(self.heap.h, self.args, [(self.cls, self.m_force), (self.cls, self.m_update)], n, stream)
 
     def read(self):
         g = self.heap.gather("Body")
@@ -411,9 +412,8 @@ class SpringSim:
         smmo.smmo_parallel_do(self.heap.h, self.heap.cls["Node"], self.m_node, self.args, stream)
 
     def step(self, n: int = 1, stream=None):
-        for _ in range(n):
-            self.spring_force(stream)
-            self.node_update(stream)
+        cs, cn = self.heap.cls["Spring"], self.heap.cls["Node"]
+        _repeat(self.heap.h, self.args, [(cs, self.m_force), (cn, self.m_node)], n, stream)
 
     def read(self):
         """Canonical state: node arrays by node id, spring arrays by spring id
@@ -645,10 +645,11 @@ class StructureSim:
         self.args.dt = dt
         self.do("AnchorPullNode", "pull", stream)
 
-    def compute_step(self, stream=None):
+    def compute_step(self, stream=None, n: int = 1):
         self.args.dt = self.dt
-        self.do("Spring", "force", stream)
-        self.do("Node", "node_update", stream)
+        c = self.heap.cls
+        _repeat(self.heap.h, self.args, [(c["Spring"], self.m["force"]), (c["Node"], self.m["node_update"])], n,
+                stream)
 
     def remove_disconnected(self, stream=None) -> int:
         """BFS from the anchor nodes, then deletion of the unvisited nodes and
@@ -685,8 +686,7 @@ class StructureSim:
 
     def iterate(self, substeps: int, stream=None) -> int:
         self.pull(self.dt * substeps, stream)
-        for _ in range(substeps):
-            self.compute_step(stream)
+        self.compute_step(stream, substeps)
         return self.remove_disconnected(stream)
 
     def read(self) -> dict:
