@@ -195,7 +195,7 @@ smmo_status launch_generation(smmo_heap *h, uint32_t cls, const void *args, hipS
     if (Which == 1) hipLaunchKernelGGL(k_gen_birth, ls.grid, ls.block, 0, st, h->v, k);
     if (Which == 2) hipLaunchKernelGGL(k_gen_alive_update, ls.grid, ls.block, 0, st, h->v, k);
     if ((s = launched("generation kernel"))) return s;
-    if (Which == 1) note_allocation(h, a.alive_class, 64ull * h->v.M);
+    if (Which == 1) note_allocation(h, a.alive_class, 64ull * h->v.M, st);
     return SMMO_OK;
 }
 

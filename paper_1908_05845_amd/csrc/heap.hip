@@ -727,12 +727,43 @@ smmo_status bind_field(const smmo_schema *s, uint32_t cls, const char *name, int
                                  "' required by this method");
 }
 
+namespace {
+// The state of class cls's list as launches on stream st will find it.  A
+// launch that is being captured does not run now, and runs again with every
+// replay: an enumeration inside the capture says nothing about the list that
+// launches outside find, and of the lists that exist when the capture begins
+// only those of classes without device allocation last through the replays.
+int &list_state(smmo_heap *h, uint32_t cls, hipStream_t st)
+{
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    unsigned long long id = 0;
+    if (hipStreamGetCaptureInfo(st, &cap, &id) != hipSuccess) {
+        (void)hipGetLastError();
+        cap = hipStreamCaptureStatusNone;
+    }
+    if (cap == hipStreamCaptureStatusNone) {
+        if (h->replayed[cls]) h->rstate[cls] = R_DIRTY;
+        return h->rstate[cls];
+    }
+    if (h->capture != id) {
+        h->capture = id;
+        for (uint32_t c = 0; c < SMMO_MAX_CLASSES; ++c)
+            h->capture_rstate[c] = h->churn[c] || h->replayed[c] ? R_DIRTY : h->rstate[c];
+    }
+    return h->capture_rstate[cls];
+}
+} // namespace
+
 smmo_status ensure_enumerated(smmo_heap *h, uint32_t cls, bool snapshot, hipStream_t st, bool split,
                               bool allow_direct)
 {
     // a do-all that uses a snapshot from smmo_snapshot walks that list as it is
     if ((h->v.snap >> cls) & 1) return SMMO_OK;
-    if (!snapshot && (h->rstate[cls] == R_SPLIT || (h->rstate[cls] == R_VALID && !split))) return SMMO_OK;
+    int &state = list_state(h, cls, st);
+    if (!snapshot && (state == R_SPLIT || (state == R_VALID && !split))) {
+        h->v.direct &= ~(1u << cls);
+        return SMMO_OK;
+    }
     // A walk that needs neither the iteration snapshot nor the packing plan
     // reads nothing of R but its entries; on a small heap the walk over all
     // blocks costs less than the enumeration launch it replaces, for a class
@@ -750,7 +781,7 @@ smmo_status ensure_enumerated(smmo_heap *h, uint32_t cls, bool snapshot, hipStre
                        split ? 1u : 0u);
     smmo_status s = launch_check("k_enumerate");
     if (s) return s;
-    h->rstate[cls] = split ? R_SPLIT : R_VALID;
+    state = split ? R_SPLIT : R_VALID;
     return SMMO_OK;
 }
 
@@ -821,12 +852,16 @@ uint32_t class_family(const smmo_schema *s, uint32_t cls)
     return fam;
 }
 
-void note_allocation(smmo_heap *h, uint32_t cls, uint64_t max_new_objects, bool in_method)
+void note_allocation(smmo_heap *h, uint32_t cls, uint64_t max_new_objects, hipStream_t st, bool in_method)
 {
     if (in_method) h->churn[cls] = true;
     const uint64_t add = (max_new_objects + 63) / 64 + 1;
     h->ub_blocks[cls] = std::min<uint64_t>(h->v.M, h->ub_blocks[cls] + add);
-    h->rstate[cls] = R_DIRTY;
+    int &state = list_state(h, cls, st);
+    state = R_DIRTY;
+    // every replay of a captured launch creates the objects again, unseen by
+    // the host: neither the class's list nor its block bound may be trusted
+    if (&state != &h->rstate[cls]) h->replayed[cls] = true;
 }
 
 } // namespace smmo
@@ -1152,7 +1187,7 @@ smmo_status smmo_parallel_new(smmo_heap *h, uint32_t class_id, uint32_t n, const
         hipLaunchKernelGGL(k_new_device, dim3(grid), dim3(256), 0, st, h->v, class_id, fs, n, out_handles);
         if ((s = launch_check("k_new_device"))) return s;
     }
-    note_allocation(h, class_id, n, false);
+    note_allocation(h, class_id, n, st, false);
     h->last = st;
     return SMMO_OK;
 }

@@ -266,7 +266,7 @@ smmo_status launch_gol(smmo_heap *h, uint32_t cls, const void *args, hipStream_t
     }
     if (Which == 2) hipLaunchKernelGGL(k_gol_birth, ls.grid, ls.block, 0, st, h->v, k);
     if ((s = launched("gol kernel"))) return s;
-    if (Which == 2) note_allocation(h, a.alive_class, 64ull * h->v.M);
+    if (Which == 2) note_allocation(h, a.alive_class, 64ull * h->v.M, st);
     return SMMO_OK;
 }
 
@@ -314,7 +314,7 @@ smmo_status run_gol_generation(smmo_heap *h, uint32_t cls, const void *args, hip
     k.death_groups = dgroups;
     hipLaunchKernelGGL(k_gol_death_birth, dim3(dgroups + lb.grid.x), lb.block, 0, st, v, k);
     if ((s = launched("gol kernel"))) return s;
-    note_allocation(h, a.alive_class, 64ull * h->v.M);
+    note_allocation(h, a.alive_class, 64ull * h->v.M, st);
     return SMMO_OK;
 }
 
@@ -444,7 +444,7 @@ smmo_status launch_transmute(smmo_heap *h, uint32_t cls, const void *args, hipSt
     const LaunchShape ls = method_shape(h, cls);
     hipLaunchKernelGGL(k_transmute, ls.grid, ls.block, 0, st, h->v, k);
     if ((s = launched("k_transmute"))) return s;
-    note_allocation(h, a.target_class, 64ull * h->v.M);
+    note_allocation(h, a.target_class, 64ull * h->v.M, st);
     return SMMO_OK;
 }
 
@@ -462,7 +462,7 @@ smmo_status launch_spawn(smmo_heap *h, uint32_t cls, const void *args, hipStream
     if (s) return s;
     hipLaunchKernelGGL(k_spawn, method_shape(h, cls).grid, method_shape(h, cls).block, 0, st, h->v, k);
     if ((s = launched("k_spawn"))) return s;
-    note_allocation(h, a.target_class, 64ull * h->v.M);
+    note_allocation(h, a.target_class, 64ull * h->v.M, st);
     return SMMO_OK;
 }
 
@@ -540,7 +540,7 @@ smmo_status launch_ls(smmo_heap *h, uint32_t cls, const void *args, hipStream_t 
     if (Which == 0) hipLaunchKernelGGL(k_ls_alloc, ls.grid, ls.block, 0, st, h->v, k);
     else hipLaunchKernelGGL(k_ls_free, ls.grid, ls.block, 0, st, h->v, k);
     if ((s = launched("alloc.ls kernel"))) return s;
-    if (Which == 0) note_allocation(h, a.target_class, (uint64_t)a.n * a.workers);
+    if (Which == 0) note_allocation(h, a.target_class, (uint64_t)a.n * a.workers, st);
     return SMMO_OK;
 }
 

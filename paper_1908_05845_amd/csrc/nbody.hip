@@ -414,7 +414,7 @@ smmo_status nbody_force_launch(smmo_heap *h, uint32_t cls, const void *args, hip
     if ((s = ensure_enumerated(h, cls, false, st))) return s;
     const uint64_t blocks = std::max<uint64_t>(1, h->ub_blocks[cls]);
     const PairShape sh = pair_shape(blocks);
-    if (sh.W && !((h->v.direct >> cls) & 1)) {
+    if (sh.W && !h->replayed[cls] && !((h->v.direct >> cls) & 1)) {
         const uint64_t I = 32 * sh.W, stride = (64 * blocks + I - 1) / I * I;
         float2 *part = static_cast<float2 *>(class_workspace(h, cls, pair_rows(64 * blocks, sh) * stride * sizeof(float2), st));
         if (part) {

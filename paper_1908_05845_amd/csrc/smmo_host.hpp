@@ -75,6 +75,13 @@ struct smmo_heap {
     // classes that methods create objects of (their lists go stale launch
     // after launch; small heaps walk them directly instead of re-enumerating)
     bool churn[SMMO_MAX_CLASSES] = {};
+    // classes that a captured launch creates objects of: replays do it again
+    // without the host's knowledge, so rstate and ub_blocks say nothing
+    bool replayed[SMMO_MAX_CLASSES] = {};
+    // the lists' states inside the capture `capture` (an id of the runtime's),
+    // for the launches captured in it; rstate is what the others find
+    unsigned long long capture = 0;
+    int capture_rstate[SMMO_MAX_CLASSES] = {};
     // classes with a snapshot from smmo_snapshot that no do-all has used yet
     // (the list R of such a class is the snapshot's)
     uint32_t snap_pending = 0;
@@ -143,7 +150,7 @@ bool packing_wanted(const smmo_heap *h, uint32_t cls, const LaunchShape &ls);
 
 // bookkeeping after a launch that creates objects of class cls (in_method:
 // a method's device allocation, not a host-side bulk creation)
-void note_allocation(smmo_heap *h, uint32_t cls, uint64_t max_new_objects, bool in_method = true);
+void note_allocation(smmo_heap *h, uint32_t cls, uint64_t max_new_objects, hipStream_t st, bool in_method = true);
 
 // A device workspace of at least `bytes` for a method over class cls, kept by
 // the heap (its contents do not survive a launch; classes have their own, so

@@ -353,8 +353,8 @@ smmo_status launch_wator(smmo_heap *h, uint32_t cls, const void *args, hipStream
     if ((s = launched("wator kernel"))) return s;
     // a fish update can create up to one fish per fish; a shark update one
     // shark per shark
-    if (Which == 4) note_allocation(h, a.fish_class, 64ull * h->ub_blocks[a.fish_class]);
-    if (Which == 5) note_allocation(h, a.shark_class, 64ull * h->ub_blocks[a.shark_class]);
+    if (Which == 4) note_allocation(h, a.fish_class, 64ull * h->ub_blocks[a.fish_class], st);
+    if (Which == 5) note_allocation(h, a.shark_class, 64ull * h->ub_blocks[a.shark_class], st);
     return SMMO_OK;
 }
 
