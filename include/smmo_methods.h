@@ -76,7 +76,10 @@ typedef struct {
  *        of +-(fx, fy); v += F / m * dt; x += v * dt.
  * "spring.link"        on Spring: writes the spring's handle into a.adj[slot_a]
  *        and (handle | 1 << 31) into b.adj[slot_b]; builds the topology after
- *        parallel_new of the nodes (adj empty) and the springs.               */
+ *        parallel_new of the nodes (adj empty) and the springs.
+ * "spring.steps"       on Spring: `steps` times "spring.force" on Spring, then
+ *        "spring.node_update" on Node, in one call (and for a small mesh in
+ *        one launch), with the results of the separate do-alls.               */
 #define SMMO_SPRING_TENSION_ONLY 1u
 typedef struct {
     uint32_t node_class;
@@ -85,6 +88,15 @@ typedef struct {
     float strain_limit;
     uint32_t flags;              /* 0 or SMMO_SPRING_TENSION_ONLY; other bits: SMMO_EINVAL */
 } smmo_spring_args;
+
+typedef struct {
+    uint32_t node_class;
+    uint32_t spring_class;
+    float dt;
+    float strain_limit;
+    uint32_t flags;              /* as smmo_spring_args */
+    uint32_t steps;
+} smmo_spring_steps_args;
 
 /* ---- spring-mass mesh with partially inlined adjacency --------------------
  * The adjacency of a node is an inner array whose first K slots are inlined

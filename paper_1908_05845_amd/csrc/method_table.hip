@@ -28,6 +28,7 @@ smmo_status launch_nbody_update(smmo_heap *h, uint32_t cls, const void *args, hi
 smmo_status launch_spring_force(smmo_heap *h, uint32_t cls, const void *args, hipStream_t st);
 smmo_status launch_spring_node_update(smmo_heap *h, uint32_t cls, const void *args, hipStream_t st);
 smmo_status launch_spring_link(smmo_heap *h, uint32_t cls, const void *args, hipStream_t st);
+smmo_status launch_spring_steps(smmo_heap *h, uint32_t cls, const void *args, hipStream_t st);
 
 // launchers defined in spring_pi.hip
 smmo_status launch_spring_pi_force(smmo_heap *h, uint32_t cls, const void *args, hipStream_t st);
@@ -116,6 +117,7 @@ const MethodEntry kMethods[] = {
     {"structure.bfs_delete", sizeof(smmo_structure_args), launch_structure_bfs_delete},
     {"structure.link", sizeof(smmo_structure_args), launch_structure_link},
     {"gol.generation", sizeof(smmo_gol_args), launch_gol_generation},
+    {"spring.steps", sizeof(smmo_spring_steps_args), launch_spring_steps},
 };
 } // namespace
 

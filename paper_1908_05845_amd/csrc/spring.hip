@@ -48,6 +48,32 @@ __device__ __forceinline__ bool spring_breaks(float dx, float dy, float L0, floa
     return strain > limit;
 }
 
+// the force of a live spring on its endpoint a, and whether the spring breaks
+// (the force is then 0)
+__device__ __forceinline__ bool spring_law(const SpringK &p, float dx, float dy, float k, float L0, float &fx,
+                                           float &fy)
+{
+    float l;
+    const bool brk = spring_breaks(dx, dy, L0, p.limit, l);
+    fx = fy = 0.f;
+    if (!brk && (!p.tension_only || l > L0)) {
+        const float c = k * (l - L0) / l;
+        fx = c * dx;
+        fy = c * dy;
+    }
+    return brk;
+}
+
+// v += F/m dt, x += v dt
+__device__ __forceinline__ void node_law(const SpringK &p, float Fx, float Fy, float m, float &x, float &y, float &vx,
+                                         float &vy)
+{
+    vx += Fx / m * p.dt;
+    vy += Fy / m * p.dt;
+    x += vx * p.dt;
+    y += vy * p.dt;
+}
+
 // Spring::compute_force (Ch.7 "structure"): Hooke's law on the length change;
 // a spring strained past the limit empties its two adjacency slots and
 // deletes itself (the thesis's remove_spring followed by destroy).  A
@@ -90,15 +116,9 @@ __device__ __forceinline__ void spring_force(const HeapView &h, const SpringK &p
 #pragma unroll
         for (int j = 0; j < U; ++j) {
             if (!own[j]) continue;
-            const float dx = xb[j] - xa[j], dy = yb[j] - ya[j];
-            float l;
-            const bool brk = live[j] && spring_breaks(dx, dy, L0[j], p.limit, l);
             float fx = 0.f, fy = 0.f;
-            if (live[j] && !brk && (!p.tension_only || l > L0[j])) {
-                const float c = k[j] * (l - L0[j]) / l;
-                fx = c * dx;
-                fy = c * dy;
-            }
+            bool brk = false;
+            if (live[j]) brk = spring_law(p, xb[j] - xa[j], yb[j] - ya[j], k[j], L0[j], fx, fy);
             // full-width stores: dead and broken slots get 0, never read
             farr<float>(h, bid[j], p.s_fx)[s] = fx;
             farr<float>(h, bid[j], p.s_fy)[s] = fy;
@@ -187,16 +207,190 @@ __global__ __launch_bounds__(1024) void k_spring_node(HeapView h, SpringK p)
 #pragma unroll
         for (int j = 0; j < U; ++j) {
             if (!live[j]) continue;
-            vx[j] += Fx[j] / m[j] * p.dt;
-            vy[j] += Fy[j] / m[j] * p.dt;
-            x[j] += vx[j] * p.dt;
-            y[j] += vy[j] * p.dt;
+            node_law(p, Fx[j], Fy[j], m[j], x[j], y[j], vx[j], vy[j]);
             farr<float>(h, bid[j], p.n_vx)[s] = vx[j];
             farr<float>(h, bid[j], p.n_vy)[s] = vy[j];
             farr<float>(h, bid[j], p.n_x)[s] = x[j];
             farr<float>(h, bid[j], p.n_y)[s] = y[j];
         }
     });
+}
+
+// ---- several steps of a small mesh in one launch ----------------------------
+// A mesh of a few dozen blocks spends its step on two launches and their
+// chains of dependent loads (7.0 us for 957 nodes and 2,748 springs, of which
+// the arithmetic is a fraction).  Here one work-group of 16 wavefronts runs
+// `steps` of them: wavefront w owns entries w, w + 16, ... of both block
+// lists, the fields of its springs and nodes stay in registers, positions and
+// forces in LDS, and two barriers separate the passes of a step.  Bound by
+// the arithmetic of one CU: 1.9 us a step there, 4.2 us for 1,936 nodes and
+// 5,633 springs (6.5 as two launches in a graph); two steps of 957 nodes cost
+// 8.9 us each in one launch, 12.1 as four.
+// Same operations in the same order as the two do-alls.  A spring that breaks
+// exerts no force from then on; its slots are emptied and released after the
+// last step, which leaves the heap as the separate launches do.  A handle that
+// names a block outside the two lists (a node or spring of another class with
+// the same field offsets) is followed in memory at every step.
+constexpr uint32_t kStepsMaxBlocks = 4096;   // heap blocks: the table of list positions
+constexpr uint32_t kNone16 = 0x7FFF, kFar16 = 0x7FFE;
+
+template <int SBW, int NBW>
+__global__ __launch_bounds__(1024) void k_spring_steps(HeapView h, SpringK p, uint32_t steps)
+{
+    __shared__ float2 s_x[NBW * 1024], s_f[SBW * 1024];
+    __shared__ uint16_t s_pos[kStepsMaxBlocks];   // list position of a block; springs' with bit 15
+    const uint32_t s = lane_id(), w = threadIdx.x >> 6;
+    const uint32_t err = ald32(h.ctrl + CTRL_ERR);
+    const BlockList SL = block_list(h, p.spring_cls), NL = block_list(h, p.node_cls);
+    if (err) return;
+    if (SL.r > 16 * SBW || NL.r > 16 * NBW || h.M > kStepsMaxBlocks) {   // beyond the host's bounds: never
+        if (threadIdx.x == 0) raise_error(h, ERR_INTERNAL);
+        return;
+    }
+    for (uint32_t b = threadIdx.x; b < h.M; b += 1024) s_pos[b] = (uint16_t)kNone16;
+    __syncthreads();
+    // this wavefront's blocks (kNoBlock where there is none)
+    uint32_t sbid[SBW], nbid[NBW];
+    uint64_t live[SBW], nlive[NBW];
+#pragma unroll
+    for (int j = 0; j < SBW; ++j) {
+        const uint32_t i = w + 16 * j;
+        sbid[j] = __builtin_amdgcn_readfirstlane(i < SL.r ? SL.at(i) : kNoBlock);
+        live[j] = 0;
+        if (sbid[j] == kNoBlock) continue;
+        if (h.type[sbid[j]] != p.spring_cls) {
+            sbid[j] = kNoBlock;
+            continue;
+        }
+        live[j] = uniform64(h.alloc_bm[sbid[j]]);
+        if (s == 0) s_pos[sbid[j]] = (uint16_t)(0x8000u | i);
+    }
+#pragma unroll
+    for (int j = 0; j < NBW; ++j) {
+        const uint32_t i = w + 16 * j;
+        nbid[j] = __builtin_amdgcn_readfirstlane(i < NL.r ? NL.at(i) : kNoBlock);
+        nlive[j] = 0;
+        if (nbid[j] == kNoBlock) continue;
+        if (h.type[nbid[j]] != p.node_cls) {
+            nbid[j] = kNoBlock;
+            continue;
+        }
+        nlive[j] = uniform64(h.alloc_bm[nbid[j]]);
+        if (s == 0) s_pos[nbid[j]] = (uint16_t)i;
+    }
+    __syncthreads();
+    // the LDS index of a handle's object among the nodes (tag 0) or springs
+    // (tag 0x8000)
+    auto index = [&](uint32_t handle, uint32_t tag) -> uint32_t {
+        const uint32_t b = handle >> 6;
+        const uint32_t pos = b < h.M ? s_pos[b] : kNone16;
+        return pos != kNone16 && (pos & 0x8000u) == tag ? ((pos & 0x7FFu) << 6 | (handle & 63)) : kFar16;
+    };
+    uint32_t ab[SBW];
+    float k[SBW], L0[SBW];
+#pragma unroll
+    for (int j = 0; j < SBW; ++j) {
+        ab[j] = 0;
+        k[j] = L0[j] = 0.f;
+        if (!((live[j] >> s) & 1)) continue;
+        k[j] = farr<float>(h, sbid[j], p.s_k)[s];
+        L0[j] = farr<float>(h, sbid[j], p.s_L0)[s];
+        ab[j] = index(farr<uint32_t>(h, sbid[j], p.s_a)[s], 0) | index(farr<uint32_t>(h, sbid[j], p.s_b)[s], 0) << 16;
+    }
+    uint32_t e[NBW][4];                    // two slots each: LDS index, bit 15: endpoint b
+    float m[NBW], x[NBW], y[NBW], vx[NBW], vy[NBW];
+#pragma unroll
+    for (int j = 0; j < NBW; ++j) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) e[j][q] = kNone16 << 16 | kNone16;
+        m[j] = x[j] = y[j] = vx[j] = vy[j] = 0.f;
+        if (nbid[j] == kNoBlock) continue;
+        // positions of free slots too, as a spring would read them
+        x[j] = farr<float>(h, nbid[j], p.n_x)[s];
+        y[j] = farr<float>(h, nbid[j], p.n_y)[s];
+        s_x[(w + 16 * j) * 64 + s] = make_float2(x[j], y[j]);
+        if (!((nlive[j] >> s) & 1)) continue;
+        vx[j] = farr<float>(h, nbid[j], p.n_vx)[s];
+        vy[j] = farr<float>(h, nbid[j], p.n_vy)[s];
+        m[j] = farr<float>(h, nbid[j], p.n_m)[s];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            const uint32_t hd = farr<uint32_t>(h, nbid[j], p.n_adj + q * p.n_adj_stride)[s];
+            const uint32_t v = hd == kNull ? kNone16 : index(hd & 0x7FFFFFFFu, 0x8000u) | (hd >> 31) << 15;
+            e[j][q / 2] = q % 2 ? (e[j][q / 2] & 0xFFFFu) | v << 16 : v;
+        }
+    }
+    __syncthreads();
+    auto node_at = [&](uint32_t i, int j, uint32_t field) {
+        if (i != kFar16) return s_x[i];
+        const uint32_t hd = farr<uint32_t>(h, sbid[j], field)[s];
+        return make_float2(fref<float>(h, hd, p.n_x), fref<float>(h, hd, p.n_y));
+    };
+    for (uint32_t t = 0; t < steps; ++t) {
+#pragma unroll
+        for (int j = 0; j < SBW; ++j) {
+            if (sbid[j] == kNoBlock) continue;
+            float fx = 0.f, fy = 0.f;
+            bool brk = false;
+            if ((live[j] >> s) & 1) {
+                const float2 a = node_at(ab[j] & 0xFFFFu, j, p.s_a), b = node_at(ab[j] >> 16, j, p.s_b);
+                brk = spring_law(p, b.x - a.x, b.y - a.y, k[j], L0[j], fx, fy);
+            }
+            s_f[(w + 16 * j) * 64 + s] = make_float2(fx, fy);
+            live[j] &= ~__ballot(brk);
+        }
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < NBW; ++j) {
+            if (!((nlive[j] >> s) & 1)) continue;
+            float Fx = 0.f, Fy = 0.f;
+#pragma unroll
+            for (int q = 0; q < 8; ++q) {
+                const uint32_t v = e[j][q / 2] >> 16 * (q % 2), i = v & 0x7FFFu;
+                if (i == kNone16) continue;
+                float2 f;
+                if (i != kFar16) {
+                    f = s_f[i];
+                } else {
+                    const uint32_t hd = farr<uint32_t>(h, nbid[j], p.n_adj + q * p.n_adj_stride)[s] & 0x7FFFFFFFu;
+                    f = make_float2(fref<float>(h, hd, p.s_fx), fref<float>(h, hd, p.s_fy));
+                }
+                if (v & 0x8000u) {
+                    Fx -= f.x;
+                    Fy -= f.y;
+                } else {
+                    Fx += f.x;
+                    Fy += f.y;
+                }
+            }
+            node_law(p, Fx, Fy, m[j], x[j], y[j], vx[j], vy[j]);
+            s_x[(w + 16 * j) * 64 + s] = make_float2(x[j], y[j]);
+        }
+        __syncthreads();
+    }
+#pragma unroll
+    for (int j = 0; j < NBW; ++j) {
+        if (!((nlive[j] >> s) & 1)) continue;
+        farr<float>(h, nbid[j], p.n_vx)[s] = vx[j];
+        farr<float>(h, nbid[j], p.n_vy)[s] = vy[j];
+        farr<float>(h, nbid[j], p.n_x)[s] = x[j];
+        farr<float>(h, nbid[j], p.n_y)[s] = y[j];
+    }
+#pragma unroll
+    for (int j = 0; j < SBW; ++j) {
+        if (sbid[j] == kNoBlock) continue;
+        const float2 f = s_f[(w + 16 * j) * 64 + s];
+        farr<float>(h, sbid[j], p.s_fx)[s] = f.x;
+        farr<float>(h, sbid[j], p.s_fy)[s] = f.y;
+        const uint64_t broken = uniform64(h.alloc_bm[sbid[j]]) & ~live[j];
+        if ((broken >> s) & 1) {
+            const uint32_t a = farr<uint32_t>(h, sbid[j], p.s_a)[s], b = farr<uint32_t>(h, sbid[j], p.s_b)[s];
+            const uint32_t qa = farr<uint8_t>(h, sbid[j], p.s_sa)[s], qb = farr<uint8_t>(h, sbid[j], p.s_sb)[s];
+            fref<uint32_t>(h, a, p.n_adj + qa * p.n_adj_stride) = kNull;
+            fref<uint32_t>(h, b, p.n_adj + qb * p.n_adj_stride) = kNull;
+        }
+        wave_release_own_block(h, p.spring_cls, sbid[j], broken);
+    }
 }
 
 // Spring::link: registers the spring in its two nodes' adjacency slots
@@ -312,9 +506,45 @@ smmo_status launch_spring(smmo_heap *h, uint32_t cls, const void *args, hipStrea
     return launched("spring kernel");
 }
 
+// spring.steps on Spring: `steps` times spring.force and spring.node_update.
+// In one launch where the mesh fits one work-group's passes and no snapshot
+// taken ahead waits for one of the two do-alls.  The line lies where the
+// registers of 16 wavefronts end, at 96 and 32 blocks: one launch is still the
+// faster there (4.2 against 6.5 us a step, see k_spring_steps).
+smmo_status run_spring_steps(smmo_heap *h, uint32_t cls, const void *args, hipStream_t st)
+{
+    smmo_spring_steps_args sa;
+    memcpy(&sa, args, sizeof sa);
+    const smmo_spring_args a{sa.node_class, sa.spring_class, sa.dt, sa.strain_limit, sa.flags};
+    SpringK k;
+    smmo_status s = cached_bind(h, (const void *)&run_spring_steps, cls, a, k, [&] { return bind_spring(h, a, k); });
+    if (s) return s;
+    if (cls != a.spring_class) return fail(SMMO_EINVAL, "spring: method runs on a different class");
+    if (sa.steps == 0) return SMMO_OK;
+    const uint64_t sb = h->ub_blocks[a.spring_class], nb = h->ub_blocks[a.node_class];
+    const uint32_t both = 1u << a.spring_class | 1u << a.node_class;
+    if (sa.steps > 1 && sb <= 96 && nb <= 32 && h->v.M <= kStepsMaxBlocks && !(h->snap_pending & both) &&
+        !h->replayed[a.spring_class] && !h->replayed[a.node_class]) {
+        if ((s = ensure_enumerated(h, a.spring_class, false, st, false, false))) return s;
+        if ((s = ensure_enumerated(h, a.node_class, false, st, false, false))) return s;
+        if (sb <= 48 && nb <= 16) hipLaunchKernelGGL((k_spring_steps<3, 1>), dim3(1), dim3(1024), 0, st, h->v, k, sa.steps);
+        else hipLaunchKernelGGL((k_spring_steps<6, 2>), dim3(1), dim3(1024), 0, st, h->v, k, sa.steps);
+        return launched("k_spring_steps");
+    }
+    // through the do-alls themselves, with their launch shapes and snapshots
+    uint32_t force = 0, node = 0;
+    if ((s = smmo_method_id("spring.force", &force)) || (s = smmo_method_id("spring.node_update", &node))) return s;
+    for (uint32_t t = 0; t < sa.steps; ++t) {
+        if ((s = smmo_parallel_do(h, a.spring_class, force, &a, sizeof a, st))) return s;
+        if ((s = smmo_parallel_do(h, a.node_class, node, &a, sizeof a, st))) return s;
+    }
+    return SMMO_OK;
+}
+
 } // namespace
 
 namespace smmo {
+smmo_status launch_spring_steps(smmo_heap *h, uint32_t c, const void *a, hipStream_t s) { return run_spring_steps(h, c, a, s); }
 smmo_status launch_spring_force(smmo_heap *h, uint32_t c, const void *a, hipStream_t s) { return launch_spring<0>(h, c, a, s); }
 smmo_status launch_spring_node_update(smmo_heap *h, uint32_t c, const void *a, hipStream_t s) { return launch_spring<1>(h, c, a, s); }
 smmo_status launch_spring_link(smmo_heap *h, uint32_t c, const void *a, hipStream_t s) { return launch_spring<2>(h, c, a, s); }

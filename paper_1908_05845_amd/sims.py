@@ -402,6 +402,7 @@ class SpringSim:
         self.m_force = smmo.smmo_method_id("spring.force")
         self.m_node = smmo.smmo_method_id("spring.node_update")
         self.m_link = smmo.smmo_method_id("spring.link")
+        self.m_steps = smmo.smmo_method_id("spring.steps")
         if S:
             smmo.smmo_parallel_do(self.heap.h, self.heap.cls["Spring"], self.m_link, self.args)
 
@@ -412,8 +413,9 @@ class SpringSim:
         smmo.smmo_parallel_do(self.heap.h, self.heap.cls["Node"], self.m_node, self.args, stream)
 
     def step(self, n: int = 1, stream=None):
-        cs, cn = self.heap.cls["Spring"], self.heap.cls["Node"]
-        _repeat(self.heap.h, self.args, [(cs, self.m_force), (cn, self.m_node)], n, stream)
+        a = self.args
+        steps = smmo.smmo_spring_steps_args(a.node_class, a.spring_class, a.dt, a.strain_limit, a.flags, n)
+        smmo.smmo_parallel_do(self.heap.h, self.heap.cls["Spring"], self.m_steps, steps, stream)
 
     def read(self):
         """Canonical state: node arrays by node id, spring arrays by spring id

@@ -86,6 +86,10 @@ class smmo_spring_args(C.Structure):
                 ("strain_limit", C.c_float), ("flags", C.c_uint32)]
 
 
+class smmo_spring_steps_args(C.Structure):
+    _fields_ = smmo_spring_args._fields_ + [("steps", C.c_uint32)]
+
+
 class smmo_adjoint_args(C.Structure):
     _fields_ = [("node_class", C.c_uint32), ("spring_class", C.c_uint32), ("dt", C.c_float),
                 ("mode", C.c_uint32), ("tape", C.c_void_p), ("tape_floats", C.c_uint64),
