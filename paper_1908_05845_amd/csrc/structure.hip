@@ -380,7 +380,8 @@ __global__ __launch_bounds__(1024) void k_st_bfs_mark(HeapView h, StructK p)
 //                          (of all slots with SMMO_BFS_DEVICE_VISITED)
 //   nbr    [+4 cap)        per dense index of a live node: its neighbours'
 //                          dense indices (the other end of each spring slot,
-//                          SMMO_NULL for an empty slot) and its handle
+//                          the node itself for an empty slot) and its
+//                          distance, SMMO_STRUCTURE_FAR until it is reached
 // The topology does not change during the search, so resolving each node's
 // springs to its neighbours once, in one wide walk, takes two dependent loads
 // out of every level's chain, and with the visited set in LDS a level's
@@ -427,9 +428,8 @@ __global__ __launch_bounds__(1024) void k_st_bfs_rank(HeapView h, StructK p, uin
     });
 }
 
-// NodeBase::initialize_frontier, appending the anchor nodes to the queue (one
-// atomic per wavefront for all of its anchors), and each live node's
-// neighbour entry
+// The anchor nodes appended to the queue (one atomic per wavefront for all of
+// its anchors), and each live node's neighbour entry
 __global__ __launch_bounds__(1024) void k_st_bfs_queue_init(HeapView h, StructK p, uint32_t *work, uint32_t cap)
 {
     const BfsLayout L = bfs_layout(cap, h.M);
@@ -445,7 +445,6 @@ __global__ __launch_bounds__(1024) void k_st_bfs_queue_init(HeapView h, StructK 
 #pragma unroll
         for (int q = 0; q < 3; ++q) hs[q] = farr<uint32_t>(h, bid, p.n_spr + q * p.n_spr_stride)[s];
         if (live) {
-            farr<int32_t>(h, bid, p.n_dist)[s] = anchor ? 0 : kFar;
             uint32_t other[3];
 #pragma unroll
             for (int q = 0; q < 3; ++q) {
@@ -460,13 +459,13 @@ __global__ __launch_bounds__(1024) void k_st_bfs_queue_init(HeapView h, StructK 
             uint32_t o[3];
 #pragma unroll
             for (int q = 0; q < 3; ++q) {
-                o[q] = kNull;
+                o[q] = self;
                 if (other[q] == kNull) continue;
                 const uint64_t di = 64ull * rank[other[q] >> 6] + (other[q] & 63);
                 if (di < cap) o[q] = (uint32_t)di;
                 else raise_error(h, ERR_INTERNAL);
             }
-            nbr[self] = make_uint4(o[0], o[1], o[2], (bid << 6) | s);
+            nbr[self] = make_uint4(o[0], o[1], o[2], (uint32_t)kFar);
         }
         const uint64_t am = __ballot(anchor);
         if (!am) return;
@@ -490,16 +489,27 @@ __global__ __launch_bounds__(1024) void k_st_bfs_queue_init(HeapView h, StructK 
 // part (up to qlim dense indices in one of two LDS buffers) followed by a
 // range of the queue in device memory (level 0: the anchors; later: the
 // appends that did not fit in LDS).  The threads share the frontier evenly:
-// each writes a node's distance d, reads its neighbour entry and claims the
-// neighbours; a node won is appended to level d + 1's frontier, at the
-// position the LDS counter d mod 3 gives: below qlim in the other LDS
-// buffer, beyond it in the queue after level d's own range.  One barrier
-// ends a level, after which every thread knows the next frontier from that
-// counter; the counter of level d + 1 was last read after the barrier that
-// ended level d - 2, so thread 0 clears it during level d.  The loop ends at
-// the first empty frontier, at most one level per node.  *levels = the
+// each reads a node's neighbour entry, stores the distance d there and claims
+// the neighbours (an empty slot names the node itself, which is visited, so
+// its claim fails without a branch); a node won is appended to level d + 1's
+// frontier, at the position the LDS counter d mod 3 gives: below qlim in the
+// other LDS buffer, beyond it in the queue after level d's own range.  One
+// barrier ends a level, after which every thread knows the next frontier from
+// that counter; the counter of level d + 1 was last read after the barrier
+// that ended level d - 2, so thread 0 clears it during level d.  The loop ends
+// at the first empty frontier, at most one level per node.  *levels = the
 // number of levels the thesis's loop runs: the non-empty ones plus the pass
 // that finds the frontier empty.
+// Bound by what one CU issues and waits for per level: one chain of LDS
+// frontier entry, neighbour entry (the only load from device memory), three
+// LDS claims, one LDS add, barrier, with a thousand frontier nodes' instructions
+// on four SIMDs beside it.  So the common case has a loop of its own: every
+// slot in the LDS bitmap, at most one node per thread, no address but a
+// 32-bit offset: 1.83 ms for the 1,084 levels of a damaged 1000 x 1000 mesh
+// (1.99 ms with 64-bit addresses, a select per claim and the distance written
+// to the node).  A level costs 0.62 us in latency and 0.8 ns per node; neither
+// half-sized entries nor the distance's store change that, and loads that
+// bypass the caches cost up to 1.6 times as much.
 __global__ __launch_bounds__(kBfsThreads) void k_st_bfs_levels(HeapView h, StructK p, uint32_t *work, uint32_t cap,
                                                         uint32_t options, uint32_t *levels)
 {
@@ -509,7 +519,7 @@ __global__ __launch_bounds__(kBfsThreads) void k_st_bfs_levels(HeapView h, Struc
     const BfsLayout L = bfs_layout(cap, h.M);
     uint32_t *queue = work + L.queue;
     uint32_t *gbits = work + L.bits;
-    const uint4 *nbr = reinterpret_cast<const uint4 *>(work + L.nbr);
+    uint4 *nbr = reinterpret_cast<uint4 *>(work + L.nbr);
     const uint32_t lds_bits = (options & SMMO_BFS_DEVICE_VISITED) ? 0u : kBfsLdsBits;
     const uint32_t qlim = (options & SMMO_BFS_SMALL_FRONTIER) ? 64u : kBfsLdsQ;
     for (uint32_t w = threadIdx.x; w < kBfsLdsWords; w += kBfsThreads) s_bits[w] = 0u;
@@ -532,53 +542,55 @@ __global__ __launch_bounds__(kBfsThreads) void k_st_bfs_levels(HeapView h, Struc
         return (atomicOr(&gbits[o >> 5], bit) & bit) == 0;
     };
     uint32_t nl = 0;                 // LDS part of the frontier, in s_q[cur]
-    uint32_t glo = 0, ghi = s_n0;    // queue part of the frontier
+    uint32_t glo = 0, ghi = __builtin_amdgcn_readfirstlane(s_n0);    // queue part of the frontier
     for (uint32_t i = threadIdx.x; i < ghi; i += kBfsThreads)
         if (!claim(queue[i], std::false_type{})) raise_error(h, ERR_INTERNAL);   // an anchor listed twice
     __syncthreads();
     uint32_t cur = 0;
-    uint32_t d = 0;
-    // one level: each node's three claims issued together (a missing
-    // neighbour's claim is aimed at the node itself, visited already, so it
-    // fails without a branch), then one append for all the node won, then
-    // the node's distance (a store nothing in the level waits for)
+    uint32_t d = 0, c0 = 0, c1 = 1, c2 = 2;        // the level and the counters of d, d + 1, d + 2 (mod 3)
+    // one node of the frontier: the three claims issued together, then one
+    // append for all the nodes won
     auto node = [&](uint32_t self, auto lds_only) {
-        uint32_t *cnt = &s_cnt[d % 3];
-        const uint4 e = nbr[self];
+        const uint32_t off = decltype(lds_only)::value ? self << 4 : 0u;
+        uint4 *const at = decltype(lds_only)::value ? reinterpret_cast<uint4 *>(reinterpret_cast<char *>(nbr) + off)
+                                                    : nbr + self;
+        const uint4 e = *at;
         const uint32_t o[3] = {e.x, e.y, e.z};
         bool won[3];
 #pragma unroll
-        for (int q = 0; q < 3; ++q) won[q] = claim(o[q] == kNull ? self : o[q], lds_only);
-        const uint32_t n = (uint32_t)won[0] + (uint32_t)won[1] + (uint32_t)won[2];
-        // the wavefront's appends reserved by one LDS add: each lane's offset
-        // is the sum of n over the active lanes below it, from ballots of n's
-        // two bits (a per-lane add with a varying n would be turned into a
-        // loop over the lanes)
-        const uint64_t b0 = __ballot(n & 1), b1 = __ballot(n & 2);
-        const uint64_t below = (1ull << lane_id()) - 1;
-        const uint32_t tot = (uint32_t)(__popcll(b0) + 2 * __popcll(b1));
+        for (int q = 0; q < 3; ++q) won[q] = claim(o[q], lds_only);
+        at->w = d;
+        // the wavefront's appends reserved by one LDS add: first those of
+        // slot 0, lane by lane, then those of slots 1 and 2
+        const uint64_t m0 = __ballot(won[0]), m1 = __ballot(won[1]), m2 = __ballot(won[2]);
+        const uint32_t n0 = (uint32_t)__popcll(m0), n1 = (uint32_t)__popcll(m1), n2 = (uint32_t)__popcll(m2);
+        const uint32_t tot = n0 + n1 + n2;
+        if (!tot) return;            // (uniform over the active lanes)
         uint32_t base = 0;
-        if (tot) {   // (uniform over the active lanes)
-            const uint32_t leader = (uint32_t)(__ffsll((unsigned long long)__ballot(1)) - 1);
-            if (lane_id() == leader) base = atomicAdd(cnt, tot);
-            base = __builtin_amdgcn_readfirstlane(base);   // the leader is the first active lane
-        }
-        if (n) {
-            uint32_t pos = base + (uint32_t)(__popcll(b0 & below) + 2 * __popcll(b1 & below));
+        const uint32_t leader = (uint32_t)(__ffsll((unsigned long long)__ballot(1)) - 1);
+        if (lane_id() == leader) base = atomicAdd(&s_cnt[c0], tot);
+        base = __builtin_amdgcn_readfirstlane(base);   // the leader is the first active lane
+        auto rank = [](uint64_t m) {
+            return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+        };
+        const uint32_t pos[3] = {base + rank(m0), base + n0 + rank(m1), base + n0 + n1 + rank(m2)};
+        if (base + tot <= qlim) {
 #pragma unroll
-            for (int q = 0; q < 3; ++q) {
-                if (!won[q]) continue;
-                if (pos < qlim) {
-                    s_q[cur ^ 1][pos] = o[q];
-                } else {
-                    const uint32_t g = ghi + (pos - qlim);
-                    if (g < cap) queue[g] = o[q];
-                    else raise_error(h, ERR_INTERNAL);
-                }
-                ++pos;
+            for (int q = 0; q < 3; ++q)
+                if (won[q]) s_q[cur ^ 1][pos[q]] = o[q];
+            return;
+        }
+#pragma unroll
+        for (int q = 0; q < 3; ++q) {
+            if (!won[q]) continue;
+            if (pos[q] < qlim) {
+                s_q[cur ^ 1][pos[q]] = o[q];
+            } else {
+                const uint32_t g = ghi + (pos[q] - qlim);
+                if (g < cap) queue[g] = o[q];
+                else raise_error(h, ERR_INTERNAL);
             }
         }
-        fref<int32_t>(h, e.w, p.n_dist) = (int32_t)d;
     };
     // the frontier's LDS part and its queue part in separate branches, so
     // that each read is an LDS or a global load (not a flat one)
@@ -592,18 +604,48 @@ __global__ __launch_bounds__(kBfsThreads) void k_st_bfs_levels(HeapView h, Struc
     const bool lds_only = cap <= lds_bits;
     for (;;) {
         if (nl + (ghi - glo) == 0) break;
-        if (threadIdx.x == 0) s_cnt[(d + 1) % 3] = 0;
-        if (lds_only) level(std::true_type{});
-        else level(std::false_type{});
+        if (threadIdx.x == 0) s_cnt[c1] = 0;
+        if (lds_only && glo == ghi && nl <= kBfsThreads) {
+            if (threadIdx.x < nl) node(s_q[cur][threadIdx.x], std::true_type{});
+        } else if (lds_only) {
+            level(std::true_type{});
+        } else {
+            level(std::false_type{});
+        }
         __syncthreads();
-        const uint32_t appended = s_cnt[d % 3];   // final: every append of the level precedes the barrier
+        // final: every append of the level precedes the barrier
+        const uint32_t appended = __builtin_amdgcn_readfirstlane(s_cnt[c0]);
         nl = std::min(appended, qlim);
         glo = ghi;
         ghi = std::min(ghi + (appended - nl), cap);
         cur ^= 1;
         ++d;
+        const uint32_t c = c0;
+        c0 = c1;
+        c1 = c2;
+        c2 = c;
     }
     if (threadIdx.x == 0) *levels = d + 1;
+}
+
+// The distances from the neighbour entries to the nodes, and
+// NodeBase::delete_node: an unvisited node flags its springs
+__global__ __launch_bounds__(1024) void k_st_bfs_finish(HeapView h, StructK p, const uint32_t *work, uint32_t cap)
+{
+    const uint32_t *dist = work + bfs_layout(cap, h.M).nbr + 3;
+    for_each_family_block(h, p.fam_mask, p.wpg, [&](uint32_t bid, uint64_t bm, uint32_t, uint32_t i) {
+        if (64ull * i + 64 > cap) return;   // (the rank pass has raised the error)
+        const uint32_t s = lane_id();
+        const int32_t d = (int32_t)dist[4 * (64ull * i + s)];      // issued beside the header loads
+        if (!((bm >> s) & 1)) return;
+        farr<int32_t>(h, bid, p.n_dist)[s] = d;
+        if (d != kFar) return;
+#pragma unroll
+        for (int q = 0; q < 3; ++q) {
+            const uint32_t hs = farr<uint32_t>(h, bid, p.n_spr + q * p.n_spr_stride)[s];
+            if (hs != kNull && st_valid(h, hs & ~kP2)) fref<uint8_t>(h, hs & ~kP2, p.s_del) = 1;
+        }
+    });
 }
 
 // Spring::delete_spring
@@ -813,16 +855,16 @@ smmo_status remove_disconnected(smmo_heap *h, const smmo_structure_args &a, uint
         if (((k.fam_mask >> c) & 1) && (s = ensure_enumerated(h, c, false, st, false, false))) return s;
     const uint32_t cap = (uint32_t)slots;
     hipLaunchKernelGGL(k_st_bfs_clear, dim3(1), dim3(kBfsHeader), 0, st, work);
+    const LaunchShape shape = family_shape(h, a.nodebase_class, k.fam_mask);
     if (k.fam_mask) {
-        LaunchShape ls = family_shape(h, a.nodebase_class, k.fam_mask);
-        k.wpg = ls.block.x / 64;
-        hipLaunchKernelGGL(k_st_bfs_rank, ls.grid, ls.block, 0, st, h->v, k, work, cap);
-        hipLaunchKernelGGL(k_st_bfs_queue_init, ls.grid, ls.block, 0, st, h->v, k, work, cap);
+        k.wpg = shape.block.x / 64;
+        hipLaunchKernelGGL(k_st_bfs_rank, shape.grid, shape.block, 0, st, h->v, k, work, cap);
+        hipLaunchKernelGGL(k_st_bfs_queue_init, shape.grid, shape.block, 0, st, h->v, k, work, cap);
     }
     hipLaunchKernelGGL(k_st_bfs_levels, dim3(1), dim3(kBfsThreads), 0, st, h->v, k, work, cap, a.bfs_options, levels);
+    if (k.fam_mask) hipLaunchKernelGGL(k_st_bfs_finish, shape.grid, shape.block, 0, st, h->v, k, work, cap);
     if ((s = launched("structure BFS kernel"))) return s;
     h->last = st;
-    if ((s = launch_structure<W_BFS_MARK>(h, a.nodebase_class, &a, st))) return s;
     return launch_structure<W_BFS_DELETE>(h, a.spring_class, &a, st);
 }
 
