@@ -791,10 +791,10 @@ bool packing_wanted(const smmo_heap *h, uint32_t cls, const LaunchShape &ls)
     return h->cfg.sparse_packing == 2 || (h->cfg.sparse_packing == 1 && h->ub_blocks[cls] > waves);
 }
 
-LaunchShape method_shape(const smmo_heap *h, uint32_t cls, uint32_t def_group)
+LaunchShape method_shape(const smmo_heap *h, uint32_t cls, uint32_t def_group, uint32_t def_wg, uint32_t def_waves_per_cu)
 {
-    uint32_t wg = 256;
-    uint64_t waves = h->cfg.grid_waves ? h->cfg.grid_waves : 64ull * h->cu_count;
+    uint32_t wg = def_wg;
+    uint64_t waves = h->cfg.grid_waves ? h->cfg.grid_waves : (uint64_t)def_waves_per_cu * h->cu_count;
     uint32_t group = def_group == 0 ? 1 : h->cfg.block_group ? h->cfg.block_group : def_group;
     if (h->cur_method < 64) {
         if (h->launch_wg[h->cur_method][cls]) wg = h->launch_wg[h->cur_method][cls];

@@ -131,8 +131,10 @@ smmo_status ensure_enumerated(smmo_heap *h, uint32_t cls, bool snapshot, hipStre
 
 
 // launch shape of a do-all over class cls: the (method, class) setting of
-// smmo_set_launch if any, else 256-thread work-groups and 64 wavefronts per
-// CU, never more wavefronts than the class has groups of blocks; group =
+// smmo_set_launch if any, else the method's default (256-thread work-groups
+// and 64 wavefronts per CU unless it says otherwise; the heap's grid_waves
+// goes before the wavefronts), never more wavefronts than the class has
+// groups of blocks; group =
 // blocks a wavefront takes per iteration: 1 for a method without groups
 // (def_group 0), else the setting, else the heap's block_group, else the
 // method's default def_group
@@ -141,7 +143,8 @@ struct LaunchShape {
     dim3 block;
     uint32_t group;
 };
-LaunchShape method_shape(const smmo_heap *h, uint32_t cls, uint32_t def_group = 0);
+LaunchShape method_shape(const smmo_heap *h, uint32_t cls, uint32_t def_group = 0, uint32_t def_wg = 256,
+                         uint32_t def_waves_per_cu = 64);
 
 // whether a packed do-all of class cls launched with shape ls should get a
 // list with the packing plan (sparse_packing 2, or 1 with a class that may

@@ -445,8 +445,14 @@ smmo_status bind_spring(smmo_heap *h, const smmo_spring_args &a, SpringK &k)
     return SMMO_OK;
 }
 
-// blocks per wavefront iteration of the spring do-alls unless set otherwise
-constexpr uint32_t kSpringGroup = 1;
+// Default launch shapes (us a step, one do-all's shape varied; 1000 x 1000,
+// 600 x 500 and 224 meshes of 3.5M nodes).  Both take work-groups of two
+// wavefronts, which fill the last gaps of a CU better than four.  The force
+// pass runs best with one grid that is resident all at once, 32 wavefronts per
+// CU: 33.5, 14.7 and 132.8 against 34.8, 16.0 and 135.6 with 64.  The node
+// pass keeps 64 (33.6, 15.6), and beyond the MALL, where its two rounds of
+// loads wait longest, takes two blocks at a time: 125.9 against 135.6.
+constexpr uint32_t kSpringWg = 128, kForceWaves = 32, kNodeWaves = 64;
 
 // the MALL (Infinity Cache) of an MI355X, in front of HBM
 constexpr uint64_t kMallBytes = 256ull << 20;
@@ -479,9 +485,10 @@ smmo_status launch_spring(smmo_heap *h, uint32_t cls, const void *args, hipStrea
     if (cls != (Which == 1 ? a.node_class : a.spring_class))
         return fail(SMMO_EINVAL, "spring: method runs on a different class");
     if ((s = ensure_enumerated(h, cls, false, st))) return s;
-    const LaunchShape ls = method_shape(h, cls, kSpringGroup);
-    k.wpg = ls.block.x / 64;
     const bool nt = Which != 2 && streaming(h, k);
+    const LaunchShape ls = Which == 0 ? method_shape(h, cls, 1, kSpringWg, kForceWaves)
+                                      : method_shape(h, cls, Which == 1 && nt ? 2 : 1, kSpringWg, kNodeWaves);
+    k.wpg = ls.block.x / 64;
     if (Which == 0) {
         if (ls.group == 4) nt ? launch_force<4, true>(ls, st, h->v, k) : launch_force<4, false>(ls, st, h->v, k);
         else if (ls.group == 2) nt ? launch_force<2, true>(ls, st, h->v, k) : launch_force<2, false>(ls, st, h->v, k);
