@@ -147,6 +147,16 @@ typedef struct {
  *                             non-NULL tape the new (x, y) also go to tape
  *                             plane pair `slot`, by handle (tape NULL: no
  *                             tape, tape_floats and plane unused)
+ * "adjoint.step"   on Node  : a whole forward step (two-sided springs, none
+ *                             breaking) in one pass over the nodes, as
+ *                             smmo_adjoint_pass_args says, with the positions
+ *                             and velocities that "spring.force" and
+ *                             "adjoint.step_node" compute; fx, fy stay as
+ *                             they are
+ * "adjoint.reverse" on Node : a whole reverse step in one pass over the
+ *                             nodes, with the lx, ly, lvx, lvy and gk that
+ *                             "adjoint.spring" and "adjoint.node" (mode 3)
+ *                             compute; cx, cy, wx, wy stay as they are
  * The tape holds planes of `plane` floats (plane >= 64 * heap blocks, one
  * float per handle); tape_floats is its capacity, checked on the host.
  * seed arrays have seed_count entries, indexed by the node's id field.     */
@@ -165,6 +175,31 @@ typedef struct {
     const float *seed_vx;
     const float *seed_vy;
 } smmo_adjoint_args;
+
+/* Passes that compute every spring at both of its nodes.  A node reads its
+ * neighbours' values from planes (device arrays of `plane` >= 64 * heap blocks
+ * floats, one per handle) that the same pass does not write:
+ * "adjoint.step":    px, py = all nodes' positions before the step (equal to
+ *                    the fields x, y); the new ones go to x, y and to out_x,
+ *                    out_y, which must be other planes.  wx, wy unused.
+ * "adjoint.reverse": px, py = positions x_n; wx, wy = w of step n, or NULL:
+ *                    no spring terms.  lx, ly take the springs' terms, gk is
+ *                    accumulated; then with out_x, out_y (other planes than
+ *                    wx, wy) mu, lv and w of the step before, w to out_x,
+ *                    out_y; NULL: the spring terms alone. */
+typedef struct {
+    uint32_t node_class;
+    uint32_t spring_class;
+    float dt;
+    uint32_t reserved;           /* 0 */
+    uint64_t plane;
+    const float *px;
+    const float *py;
+    const float *wx;
+    const float *wy;
+    float *out_x;
+    float *out_y;
+} smmo_adjoint_pass_args;
 
 /* ---- test methods ---------------------------------------------------------
  * "test.axpy"      on any class with F32 field "x": x = a * x + b

@@ -32,6 +32,45 @@ struct AdjK {
     uint32_t wpg;             // wavefronts per work-group of this launch
 };
 
+// v += F/m dt, x += v dt
+__device__ __forceinline__ void adj_advance(float dt, float Fx, float Fy, float m, float &x, float &y, float &vx,
+                                            float &vy)
+{
+    vx += Fx / m * dt;
+    vy += Fy / m * dt;
+    x += vx * dt;
+    y += vy * dt;
+}
+
+// The laws of the reverse step, with the fused multiply-adds written out so
+// that every kernel rounds alike.
+// mu = lv + dt lx (into lv), w = mu / m
+__device__ __forceinline__ void adj_weigh(float dt, float lx, float ly, float m, float &lvx, float &lvy, float &wx,
+                                          float &wy)
+{
+    lvx = fmaf(dt, lx, lvx);
+    lvy = fmaf(dt, ly, lvy);
+    wx = lvx / m;
+    wy = lvy / m;
+}
+
+// a spring's terms from d = x_b - x_a and g = w_a - w_b: c = dt K g, and
+// dt (l - L0) (u.g) added to dL/dk
+__device__ __forceinline__ void adj_spring_terms(float dt, float dx, float dy, float gx, float gy, float k, float L0,
+                                                 float &cx, float &cy, float &gk)
+{
+#pragma clang fp contract(off)
+    const float l = sqrtf(fmaf(dx, dx, dy * dy));
+    const float ux = dx / l, uy = dy / l;
+    const float ug = fmaf(ux, gx, uy * gy);
+    const float r = L0 / l, r1 = 1.f - r;
+    const float kgx = k * fmaf(r1, gx, r * ux * ug);
+    const float kgy = k * fmaf(r1, gy, r * uy * ug);
+    cx = dt * kgx;
+    cy = dt * kgy;
+    gk = fmaf(dt * (l - L0), ug, gk);
+}
+
 struct AdjKey {
     uint32_t node_class, spring_class;
 };
@@ -114,10 +153,7 @@ __global__ __launch_bounds__(1024) void k_adj_step_node(HeapView h, AdjK p)
 #pragma unroll
         for (int j = 0; j < U; ++j) {
             if (!live[j]) continue;
-            vx[j] += Fx[j] / m[j] * p.dt;
-            vy[j] += Fy[j] / m[j] * p.dt;
-            x[j] += vx[j] * p.dt;
-            y[j] += vy[j] * p.dt;
+            adj_advance(p.dt, Fx[j], Fy[j], m[j], x[j], y[j], vx[j], vy[j]);
             farr<float>(h, bid[j], p.n_vx)[s] = vx[j];
             farr<float>(h, bid[j], p.n_vy)[s] = vy[j];
             farr<float>(h, bid[j], p.n_x)[s] = x[j];
@@ -195,7 +231,7 @@ __global__ __launch_bounds__(1024) void k_adj_node(HeapView h, AdjK p)
         // before the header is used and before the gathers of the first part
         float lx = farr<float>(h, bid, p.n_lx)[s], ly = farr<float>(h, bid, p.n_ly)[s];
         const float m = farr<float>(h, bid, p.n_m)[s];
-        const float lvx = farr<float>(h, bid, p.n_lvx)[s], lvy = farr<float>(h, bid, p.n_lvy)[s];
+        float lvx = farr<float>(h, bid, p.n_lvx)[s], lvy = farr<float>(h, bid, p.n_lvy)[s];
         uint32_t e[8];
         if (p.mode & 1u) {
 #pragma unroll
@@ -220,12 +256,12 @@ __global__ __launch_bounds__(1024) void k_adj_node(HeapView h, AdjK p)
             farr<float>(h, bid, p.n_ly)[s] = ly;
         }
         if (p.mode & 2u) {
-            const float mux = lvx + p.dt * lx;
-            const float muy = lvy + p.dt * ly;
-            farr<float>(h, bid, p.n_wx)[s] = mux / m;
-            farr<float>(h, bid, p.n_wy)[s] = muy / m;
-            farr<float>(h, bid, p.n_lvx)[s] = mux;
-            farr<float>(h, bid, p.n_lvy)[s] = muy;
+            float wx, wy;
+            adj_weigh(p.dt, lx, ly, m, lvx, lvy, wx, wy);
+            farr<float>(h, bid, p.n_wx)[s] = wx;
+            farr<float>(h, bid, p.n_wy)[s] = wy;
+            farr<float>(h, bid, p.n_lvx)[s] = lvx;
+            farr<float>(h, bid, p.n_lvy)[s] = lvy;
         }
     });
 }
@@ -244,17 +280,171 @@ __global__ __launch_bounds__(1024) void k_adj_spring(HeapView h, AdjK p)
         const float L0 = farr<float>(h, bid, p.s_L0)[s];
         if (!((hd.bm(0) >> s) & 1)) return;
         const float dx = px[b] - px[a], dy = py[b] - py[a];
-        const float l = sqrtf(dx * dx + dy * dy);
-        const float ux = dx / l, uy = dy / l;
         const float gx = fref<float>(h, a, p.n_wx) - fref<float>(h, b, p.n_wx);
         const float gy = fref<float>(h, a, p.n_wy) - fref<float>(h, b, p.n_wy);
-        const float ug = ux * gx + uy * gy;
-        const float r = L0 / l;
-        const float kgx = k * ((1.f - r) * gx + r * ux * ug);
-        const float kgy = k * ((1.f - r) * gy + r * uy * ug);
-        farr<float>(h, bid, p.s_cx)[s] = p.dt * kgx;
-        farr<float>(h, bid, p.s_cy)[s] = p.dt * kgy;
-        farr<float>(h, bid, p.s_gk)[s] += p.dt * (l - L0) * ug;
+        float cx, cy, gk = farr<float>(h, bid, p.s_gk)[s];
+        adj_spring_terms(p.dt, dx, dy, gx, gy, k, L0, cx, cy, gk);
+        farr<float>(h, bid, p.s_cx)[s] = cx;
+        farr<float>(h, bid, p.s_cy)[s] = cy;
+        farr<float>(h, bid, p.s_gk)[s] = gk;
+    });
+}
+
+// ---- a step in one pass over the nodes -------------------------------------
+// On a mesh that stays in the caches a step's two launches, each near the
+// launch floor, cost more than the arithmetic, so each node computes all of
+// its springs itself (every spring twice, bit for bit alike at both ends) and
+// reads its neighbours' values from planes that the pass does not write.
+// Bound by the chain of four dependent loads (slots, springs, neighbours'
+// values) and the launch: 100k nodes, 100 steps forward 0.81 ms and the
+// checkpointed sweep 1.47 ms, as launched; 1.04 and 1.91 ms as separate spring
+// and node passes (262k nodes: 1.12 and 2.39 against 1.41 and 2.63).
+struct AdjPass {
+    const float *px, *py, *wx, *wy;
+    float *ox, *oy;
+};
+
+// the springs at a node's slots: for each used slot the other end's handle,
+// stiffness and rest length (an unused slot loads from handle 0, so that no
+// branch separates the loads of the eight slots)
+struct SlotSprings {
+    uint32_t spring[8], other[8];
+    float k[8], L0[8];
+    bool use[8], is_b[8];
+};
+
+__device__ __forceinline__ void load_slots(const HeapView &h, const AdjK &p, const uint32_t *e, bool live,
+                                           SlotSprings &q)
+{
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        q.use[i] = live && e[i] != kNull;
+        q.is_b[i] = (e[i] >> 31) != 0;
+        q.spring[i] = q.use[i] ? e[i] & 0x7FFFFFFFu : 0u;
+    }
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        q.other[i] = fref<uint32_t>(h, q.spring[i], q.is_b[i] ? p.s_a : p.s_b);
+        q.k[i] = fref<float>(h, q.spring[i], p.s_k);
+        q.L0[i] = fref<float>(h, q.spring[i], p.s_L0);
+    }
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+        if (!q.use[i]) q.other[i] = 0;
+}
+
+// the force that k_spring_force stores for a spring that cannot break
+__device__ __forceinline__ void spring_pull(float dx, float dy, float k, float L0, float &fx, float &fy)
+{
+#pragma clang fp contract(off)
+    const float dy2 = dy * dy;
+    const float l = __builtin_sqrtf(__builtin_fmaf(dx, dx, dy2));
+    const float c = k * (l - L0) / l;
+    fx = c * dx;
+    fy = c * dy;
+}
+
+// sums without contraction: each term is rounded, as the stored one is
+__device__ __forceinline__ float add_term(float s, float t, bool minus)
+{
+#pragma clang fp contract(off)
+    return minus ? s - t : s + t;
+}
+
+__global__ __launch_bounds__(1024) void k_adj_pass_step(HeapView h, AdjK p, AdjPass q)
+{
+    const uint32_t s = lane_id();
+    for_each_block_heads<1>(h, p.node_cls, p.wpg, [&](const BlockHeads<1> &hd) {
+        const uint32_t bid = hd.bid[0];
+        uint32_t e[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) e[i] = farr<uint32_t>(h, bid, p.n_adj + i * p.n_adj_stride)[s];
+        const float m = farr<float>(h, bid, p.n_m)[s];
+        float x = farr<float>(h, bid, p.n_x)[s], y = farr<float>(h, bid, p.n_y)[s];
+        float vx = farr<float>(h, bid, p.n_vx)[s], vy = farr<float>(h, bid, p.n_vy)[s];
+        const bool live = (hd.bm(0) >> s) & 1;
+        SlotSprings sp;
+        load_slots(h, p, e, live, sp);
+        float ox[8], oy[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            ox[i] = q.px[sp.other[i]];
+            oy[i] = q.py[sp.other[i]];
+        }
+        if (!live) return;
+        float Fx = 0.f, Fy = 0.f;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            if (!sp.use[i]) continue;
+            const float dx = sp.is_b[i] ? x - ox[i] : ox[i] - x, dy = sp.is_b[i] ? y - oy[i] : oy[i] - y;
+            float fx, fy;
+            spring_pull(dx, dy, sp.k[i], sp.L0[i], fx, fy);
+            Fx = add_term(Fx, fx, sp.is_b[i]);
+            Fy = add_term(Fy, fy, sp.is_b[i]);
+        }
+        adj_advance(p.dt, Fx, Fy, m, x, y, vx, vy);
+        farr<float>(h, bid, p.n_vx)[s] = vx;
+        farr<float>(h, bid, p.n_vy)[s] = vy;
+        farr<float>(h, bid, p.n_x)[s] = x;
+        farr<float>(h, bid, p.n_y)[s] = y;
+        const uint32_t self = (bid << 6) | s;
+        q.ox[self] = x;
+        q.oy[self] = y;
+    });
+}
+
+template <bool kSprings>
+__global__ __launch_bounds__(1024) void k_adj_pass_reverse(HeapView h, AdjK p, AdjPass q)
+{
+    const uint32_t s = lane_id();
+    for_each_block_heads<1>(h, p.node_cls, p.wpg, [&](const BlockHeads<1> &hd) {
+        const uint32_t bid = hd.bid[0], self = (bid << 6) | s;
+        float lx = farr<float>(h, bid, p.n_lx)[s], ly = farr<float>(h, bid, p.n_ly)[s];
+        const float m = farr<float>(h, bid, p.n_m)[s];
+        float lvx = farr<float>(h, bid, p.n_lvx)[s], lvy = farr<float>(h, bid, p.n_lvy)[s];
+        const bool live = (hd.bm(0) >> s) & 1;
+        if constexpr (kSprings) {
+            uint32_t e[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) e[i] = farr<uint32_t>(h, bid, p.n_adj + i * p.n_adj_stride)[s];
+            const float x = q.px[self], y = q.py[self], wx = q.wx[self], wy = q.wy[self];
+            SlotSprings sp;
+            load_slots(h, p, e, live, sp);
+            float ox[8], oy[8], owx[8], owy[8], gk[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                ox[i] = q.px[sp.other[i]];
+                oy[i] = q.py[sp.other[i]];
+                owx[i] = q.wx[sp.other[i]];
+                owy[i] = q.wy[sp.other[i]];
+                gk[i] = fref<float>(h, sp.spring[i], p.s_gk);
+            }
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                if (!sp.use[i]) continue;
+                const bool b = sp.is_b[i];
+                float cx, cy;
+                adj_spring_terms(p.dt, b ? x - ox[i] : ox[i] - x, b ? y - oy[i] : oy[i] - y,
+                                 b ? owx[i] - wx : wx - owx[i], b ? owy[i] - wy : wy - owy[i], sp.k[i], sp.L0[i], cx,
+                                 cy, gk[i]);
+                lx = add_term(lx, cx, !b);
+                ly = add_term(ly, cy, !b);
+                if (!b) fref<float>(h, sp.spring[i], p.s_gk) = gk[i];   // one end of each spring
+            }
+        }
+        if (!live) return;
+        if constexpr (kSprings) {
+            farr<float>(h, bid, p.n_lx)[s] = lx;
+            farr<float>(h, bid, p.n_ly)[s] = ly;
+        }
+        if (q.ox) {
+            float wx, wy;
+            adj_weigh(p.dt, lx, ly, m, lvx, lvy, wx, wy);
+            farr<float>(h, bid, p.n_lvx)[s] = lvx;
+            farr<float>(h, bid, p.n_lvy)[s] = lvy;
+            q.ox[self] = wx;
+            q.oy[self] = wy;
+        }
     });
 }
 
@@ -354,9 +544,45 @@ smmo_status launch_adj(smmo_heap *h, uint32_t cls, const void *args, hipStream_t
     return launched("adjoint kernel");
 }
 
+// Which: 0 adjoint.step, 1 adjoint.reverse
+template <int Which>
+smmo_status launch_adj_pass(smmo_heap *h, uint32_t cls, const void *args, hipStream_t st)
+{
+    smmo_adjoint_pass_args a;
+    memcpy(&a, args, sizeof a);
+    const AdjKey key{a.node_class, a.spring_class};
+    AdjK k;
+    smmo_status s = cached_bind(h, (const void *)&launch_adj<W_NODE>, 0u, key, k,
+                                [&] { return bind_adj(h, key, k); });
+    if (s) return s;
+    if (cls != a.node_class) return fail(SMMO_EINVAL, "adjoint: method runs on a different class");
+    if (!(a.dt == a.dt)) return fail(SMMO_EINVAL, "adjoint: dt is NaN");
+    if (a.reserved) return fail(SMMO_EINVAL, "adjoint: reserved must be 0");
+    if (a.plane < 64ull * h->v.M) return fail(SMMO_EINVAL, "adjoint: plane shorter than 64 * heap blocks");
+    const bool w = a.wx && a.wy, out = a.out_x && a.out_y;
+    if ((a.wx || a.wy) != w || (a.out_x || a.out_y) != out || (Which == 0 && !out) ||
+        ((Which == 0 || w) && (!a.px || !a.py)))
+        return fail(SMMO_EINVAL, "adjoint: a plane is NULL");
+    if (out && (a.out_x == a.out_y || a.out_x == a.px || a.out_x == a.py || a.out_y == a.px || a.out_y == a.py ||
+                (Which == 1 && (a.out_x == a.wx || a.out_x == a.wy || a.out_y == a.wx || a.out_y == a.wy))))
+        return fail(SMMO_EINVAL, "adjoint: a pass cannot write the planes it reads");
+    if ((s = ensure_enumerated(h, cls, false, st))) return s;
+    // one wavefront per work-group spreads the few blocks evenly over the CUs
+    const LaunchShape ls = method_shape(h, cls, 0, 64, 64);
+    k.dt = a.dt;
+    k.wpg = ls.block.x / 64;
+    const AdjPass q{a.px, a.py, a.wx, a.wy, a.out_x, a.out_y};
+    if (Which == 0) hipLaunchKernelGGL(k_adj_pass_step, ls.grid, ls.block, 0, st, h->v, k, q);
+    else if (w) hipLaunchKernelGGL(k_adj_pass_reverse<true>, ls.grid, ls.block, 0, st, h->v, k, q);
+    else hipLaunchKernelGGL(k_adj_pass_reverse<false>, ls.grid, ls.block, 0, st, h->v, k, q);
+    return launched("adjoint kernel");
+}
+
 } // namespace
 
 namespace smmo {
+smmo_status launch_adj_pass_step(smmo_heap *h, uint32_t c, const void *a, hipStream_t s) { return launch_adj_pass<0>(h, c, a, s); }
+smmo_status launch_adj_pass_reverse(smmo_heap *h, uint32_t c, const void *a, hipStream_t s) { return launch_adj_pass<1>(h, c, a, s); }
 smmo_status launch_adj_record(smmo_heap *h, uint32_t c, const void *a, hipStream_t s) { return launch_adj<W_RECORD>(h, c, a, s); }
 smmo_status launch_adj_save(smmo_heap *h, uint32_t c, const void *a, hipStream_t s) { return launch_adj<W_SAVE>(h, c, a, s); }
 smmo_status launch_adj_load(smmo_heap *h, uint32_t c, const void *a, hipStream_t s) { return launch_adj<W_LOAD>(h, c, a, s); }

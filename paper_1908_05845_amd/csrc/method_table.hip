@@ -53,6 +53,8 @@ smmo_status launch_structure_link(smmo_heap *h, uint32_t cls, const void *args, 
 // launchers defined in adjoint.hip
 smmo_status launch_adj_record(smmo_heap *h, uint32_t cls, const void *args, hipStream_t st);
 smmo_status launch_adj_step_node(smmo_heap *h, uint32_t cls, const void *args, hipStream_t st);
+smmo_status launch_adj_pass_step(smmo_heap *h, uint32_t cls, const void *args, hipStream_t st);
+smmo_status launch_adj_pass_reverse(smmo_heap *h, uint32_t cls, const void *args, hipStream_t st);
 smmo_status launch_adj_save(smmo_heap *h, uint32_t cls, const void *args, hipStream_t st);
 smmo_status launch_adj_load(smmo_heap *h, uint32_t cls, const void *args, hipStream_t st);
 smmo_status launch_adj_seed(smmo_heap *h, uint32_t cls, const void *args, hipStream_t st);
@@ -118,6 +120,8 @@ const MethodEntry kMethods[] = {
     {"structure.link", sizeof(smmo_structure_args), launch_structure_link},
     {"gol.generation", sizeof(smmo_gol_args), launch_gol_generation},
     {"spring.steps", sizeof(smmo_spring_steps_args), launch_spring_steps},
+    {"adjoint.step", sizeof(smmo_adjoint_pass_args), launch_adj_pass_step},
+    {"adjoint.reverse", sizeof(smmo_adjoint_pass_args), launch_adj_pass_reverse},
 };
 } // namespace
 

@@ -98,6 +98,12 @@ class smmo_adjoint_args(C.Structure):
                 ("seed_vy", C.c_void_p)]
 
 
+class smmo_adjoint_pass_args(C.Structure):
+    _fields_ = [("node_class", C.c_uint32), ("spring_class", C.c_uint32), ("dt", C.c_float),
+                ("reserved", C.c_uint32), ("plane", C.c_uint64), ("px", C.c_void_p), ("py", C.c_void_p),
+                ("wx", C.c_void_p), ("wy", C.c_void_p), ("out_x", C.c_void_p), ("out_y", C.c_void_p)]
+
+
 class smmo_handle_array(C.Structure):
     _fields_ = [("handles", C.c_void_p), ("count", C.c_uint64)]
 
