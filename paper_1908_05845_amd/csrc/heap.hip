@@ -286,13 +286,17 @@ __device__ __forceinline__ void init_object(const HeapView &h, const FieldSet &f
 // allocated (and the last one active when it is only partly filled).  Runs
 // while no other kernel uses the heap (calls on a heap are stream-ordered),
 // so plain read-modify-write suffices.
+// Bound by its chain of scans and by what its one CU can store.  A wavefront
+// looks at 64 consecutive containers, which are one container of the next
+// level, so it makes one OR per summary level, not 64; and it writes the
+// claimed ids container by container, a lane per bit.
 __global__ __launch_bounds__(1024) void k_bulk_claim(HeapView h, uint32_t cls, uint32_t need,
                                                      uint32_t partial)
 {
     __shared__ uint32_t s_w[16];
     __shared__ uint32_t s_lo, s_hi;
     if (heap_failed(h)) return;
-    const uint32_t t = threadIdx.x;
+    const uint32_t t = threadIdx.x, lane = t & 63;
     const uint32_t n0 = h.lvl_n[0];
     uint64_t *F0 = h.bm_word(BM_FREE, 0, 0);
 
@@ -316,19 +320,30 @@ __global__ __launch_bounds__(1024) void k_bulk_claim(HeapView h, uint32_t cls, u
         const uint32_t k = (uint32_t)__popcll(v);
         uint32_t T;
         const uint32_t p = block_excl_scan(k, s_w, T);
+        uint64_t taken = 0;
         if (k && found + p < need) {
-            const uint32_t take = std::min(k, need - found - p);
-            const uint64_t taken = lowest_bits(v, take);
+            taken = lowest_bits(v, std::min(k, need - found - p));
             F0[c] = v & ~taken;
-            // the container's blocks join allocated[cls] with one OR per level
+            // the container's blocks join allocated[cls]
             aor(h.bm_word(bm_alloc(cls), 0, c), taken);
-            for (uint32_t l = 1; l < h.nlev; ++l)
-                aor(h.bm_word(bm_alloc(cls), l, c >> (6 * l)), 1ull << ((c >> (6 * (l - 1))) & 63));
-            uint32_t o = found + p;
-            for (uint64_t bits = taken; bits; bits &= bits - 1)
-                h.claim[o++] = c * 64 + (uint32_t)(__ffsll((unsigned long long)bits) - 1);
-            atomicMin(&s_lo, c);
-            atomicMax(&s_hi, c);
+        }
+        const uint64_t some = __ballot(taken != 0);
+        if (some) {
+            const uint32_t c0 = c - lane;              // the wavefront's first container
+            if (lane == 0) {
+                for (uint32_t l = 1; l < h.nlev; ++l)
+                    aor(h.bm_word(bm_alloc(cls), l, c0 >> (6 * l)),
+                        l == 1 ? some : 1ull << ((c0 >> (6 * (l - 1))) & 63));
+                atomicMin(&s_lo, c0 + (uint32_t)(__ffsll((unsigned long long)some) - 1));
+                atomicMax(&s_hi, c0 + 63u - (uint32_t)__clzll((long long)some));
+            }
+            for (uint64_t g = some; g; g &= g - 1) {
+                const uint32_t from = (uint32_t)(__ffsll((unsigned long long)g) - 1);
+                const uint64_t bits = __shfl((unsigned long long)taken, (int)from);
+                const uint32_t o = found + (uint32_t)__shfl((int)p, (int)from);
+                if ((bits >> lane) & 1)
+                    h.claim[o + (uint32_t)__popcll(bits & ((1ull << lane) - 1))] = (c0 + from) * 64 + lane;
+            }
         }
         found += T;
     }
@@ -337,13 +352,10 @@ __global__ __launch_bounds__(1024) void k_bulk_claim(HeapView h, uint32_t cls, u
     for (uint32_t l = 1; l < h.nlev; ++l) {
         lo >>= 6;
         hi >>= 6;
-        for (uint32_t j = lo + t; j <= hi; j += blockDim.x) {
-            uint64_t v = 0;
-            for (uint32_t b = 0; b < 64; ++b) {
-                const uint32_t child = j * 64 + b;
-                if (child < h.lvl_n[l - 1] && *h.bm_word(BM_FREE, l - 1, child) != 0) v |= 1ull << b;
-            }
-            *h.bm_word(BM_FREE, l, j) = v;
+        for (uint32_t j = lo + (t >> 6); j <= hi; j += blockDim.x >> 6) {
+            const uint32_t child = j * 64 + lane;
+            const uint64_t v = __ballot(child < h.lvl_n[l - 1] && *h.bm_word(BM_FREE, l - 1, child) != 0);
+            if (lane == 0) *h.bm_word(BM_FREE, l, j) = v;
         }
         __syncthreads();
     }
@@ -355,31 +367,24 @@ __global__ __launch_bounds__(1024) void k_bulk_claim(HeapView h, uint32_t cls, u
     }
 }
 
-// Block headers of the claimed blocks (type, allocation bitmap): one thread
-// per block, any number of work-groups.  The heap is quiescent during a bulk
-// parallel_new, so the launch boundaries order these stores against the
-// bitmaps written by k_bulk_claim.
-__global__ __launch_bounds__(256) void k_bulk_headers(HeapView h, uint32_t cls, uint32_t need, uint32_t partial)
-{
-    if (heap_failed(h)) return;
-    for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < need; i += gridDim.x * blockDim.x) {
-        const uint32_t bid = h.claim[i];
-        const bool full = !(partial && i == need - 1);
-        h.type[bid] = cls;
-        h.alloc_bm[bid] = full ? ~0ull : ((1ull << partial) - 1);
-    }
-}
-
 // Fills the objects of an ordered bulk claim: object i -> block claim[i/64],
 // slot i%64 (64 consecutive objects share a block, so every field write of a
-// wavefront is one contiguous run).
-__global__ __launch_bounds__(256) void k_bulk_init(HeapView h, FieldSet fs, uint32_t n,
+// wavefront is one contiguous run), and the block's header (type, allocation
+// bitmap) with its first object.  The heap is quiescent during a bulk
+// parallel_new, so the launch boundaries order these stores against the
+// bitmaps written by k_bulk_claim.
+__global__ __launch_bounds__(256) void k_bulk_init(HeapView h, uint32_t cls, FieldSet fs, uint32_t n,
                                                    uint32_t *out_handles)
 {
     if (heap_failed(h)) return;
     const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
-    const uint32_t handle = (h.claim[i >> 6] << 6) | (uint32_t)(i & 63);
+    const uint32_t bid = h.claim[i >> 6];
+    const uint32_t handle = (bid << 6) | (uint32_t)(i & 63);
+    if ((i & 63) == 0) {
+        h.type[bid] = cls;
+        h.alloc_bm[bid] = n - i >= 64 ? ~0ull : (1ull << (n - i)) - 1;
+    }
     init_object(h, fs, handle, i);
     if (out_handles) out_handles[i] = handle;
 }
@@ -399,23 +404,87 @@ __global__ __launch_bounds__(256) void k_new_device(HeapView h, uint32_t cls, Fi
     if (out_handles) out_handles[i] = handle;
 }
 
-// Host-initiated destroy: validates each handle (live object of the class)
-// and releases it through the converged deallocation path.
+// Host-initiated destroy, first launch: frees the slots of the live objects
+// that the handles name.  No block is freed and no type changes here, so the
+// type check is a plain load and the slot's old bit tells whether the handle
+// named a live object, once for an object named twice.
+// Bound by the rate of the atomics on the blocks' bitmaps: lanes that follow
+// one another in a block, as handles in the order of creation do, make one of
+// them (a million 120 us with one a lane, 23 us so); in no order each lane
+// makes its own (a million 62 us; 165 us with a load of the bitmap before
+// each, and with the blocks' states settled by the releases).
 __global__ __launch_bounds__(256) void k_destroy(HeapView h, uint32_t cls, const uint32_t *handles,
                                                  uint32_t n)
 {
     const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (heap_failed(h)) return;
-    bool want = false;
-    uint32_t hd = kNull;
-    if (i < n) {
-        hd = handles[i];
-        const uint32_t bid = hd >> 6;
-        want = hd != kNull && bid < h.M && ald32(h.type + bid) == cls &&
-               ((ald(h.alloc_bm + bid) >> (hd & 63)) & 1);
-        if (!want) raise_error(h, ERR_BADHANDLE);
+    const uint32_t lane = lane_id(), hd = i < n ? handles[i] : kNull, bid = hd >> 6;
+    const uint64_t bit = 1ull << (hd & 63);
+    const bool named = hd != kNull && bid < h.M && h.type[bid] == cls;
+    uint64_t pending = __ballot(named);
+    uint32_t count = 0;
+    bool gone = false, bad = i < n && !named;
+    while (pending) {
+        const uint32_t leader = (uint32_t)(__ffsll((unsigned long long)pending) - 1);
+        const bool in = ((pending >> lane) & 1) && bid == (uint32_t)__builtin_amdgcn_readlane(bid, leader);
+        const uint64_t group = __ballot(in);
+        if (__popcll(group) < 8) break;
+        const uint64_t slots = wave_or64(in ? bit : 0);
+        if (lane == leader) {
+            const uint32_t k = (uint32_t)__popcll(aand(h.alloc_bm + bid, ~slots) & slots);
+            count += k;
+            bad |= k != (uint32_t)__popcll(group);
+        }
+        pending &= ~group;
     }
-    wave_deallocate(h, cls, hd, want);
+    if ((pending >> lane) & 1) {
+        gone = aand(h.alloc_bm + bid, ~bit) & bit;
+        bad |= !gone;
+    }
+    if (bad) raise_error(h, ERR_BADHANDLE);
+    count += (uint32_t)__popcll(__ballot(gone)) * (lane == 0);
+    for (int d = 1; d < 64; d <<= 1) count += (uint32_t)__shfl_xor((int)count, d);
+    if (lane == 0 && count) count_events(h, EV_DELS, count);
+}
+
+// Second launch: brings the states of the class's blocks in line with their
+// slots, 64 blocks of one container a wavefront.  A block without objects
+// becomes free (its type unset, its slots all taken, as invalidate_block
+// leaves it), one with free slots active.  Nothing else runs on the heap, so
+// a container is its wavefront's own; what passes on to the next levels goes
+// through the switches that other wavefronts' containers meet there.
+__global__ __launch_bounds__(256) void k_destroy_settle(HeapView h, uint32_t cls)
+{
+    const uint32_t lane = lane_id(), waves = gridDim.x * (blockDim.x >> 6);
+    for (uint32_t c = global_wave_id(); c < h.lvl_n[0]; c += waves) {
+        uint64_t *const alloc = h.bm_word(bm_alloc(cls), 0, c), *const active = h.bm_word(bm_active(cls), 0, c);
+        const uint64_t mine = uniform64(*alloc);
+        if (!mine) continue;
+        const uint64_t was = uniform64(*active);
+        const uint32_t bid = c * 64 + lane;
+        const uint64_t slots = (mine >> lane) & 1 ? h.alloc_bm[bid] : ~0ull;
+        const uint64_t empty = __ballot(slots == 0), some = __ballot(slots != 0 && slots != ~0ull);
+        if (!empty && some == was) continue;
+        if (slots == 0) {
+            h.type[bid] = kNull;
+            h.alloc_bm[bid] = ~0ull;
+        }
+        OpQueue q;
+        q.reset();
+        if (lane == 0) {
+            *active = some;
+            if (!was != !some && h.nlev > 1) q.op[0] = BitOp{c, (uint16_t)bm_active(cls), 1, (int8_t)(some ? 1 : -1)};
+            if (empty) {
+                *alloc = mine & ~empty;
+                if (mine == empty && h.nlev > 1) q.op[1] = BitOp{c, (uint16_t)bm_alloc(cls), 1, -1};
+                uint64_t *const free_ = h.bm_word(BM_FREE, 0, c);
+                const uint64_t f = *free_;
+                *free_ = f | empty;
+                if (!f && h.nlev > 1) q.op[2] = BitOp{c, (uint16_t)BM_FREE, 1, 1};
+            }
+        }
+        run_ops_wave(h, q);
+    }
 }
 
 // One run of a block's 64 slots that a gather copies: a field array of 1- or
@@ -1178,10 +1247,7 @@ smmo_status smmo_parallel_new(smmo_heap *h, uint32_t class_id, uint32_t n, const
         const uint32_t need = (uint32_t)(((uint64_t)n + 63) / 64);
         hipLaunchKernelGGL(k_bulk_claim, dim3(1), dim3(1024), 0, st, h->v, class_id, need, n % 64);
         if ((s = launch_check("k_bulk_claim"))) return s;
-        const uint32_t hgrid = (uint32_t)std::min<uint64_t>((need + 255) / 256, 4096);
-        hipLaunchKernelGGL(k_bulk_headers, dim3(hgrid), dim3(256), 0, st, h->v, class_id, need, n % 64);
-        if ((s = launch_check("k_bulk_headers"))) return s;
-        hipLaunchKernelGGL(k_bulk_init, dim3(grid), dim3(256), 0, st, h->v, fs, n, out_handles);
+        hipLaunchKernelGGL(k_bulk_init, dim3(grid), dim3(256), 0, st, h->v, class_id, fs, n, out_handles);
         if ((s = launch_check("k_bulk_init"))) return s;
     } else {
         hipLaunchKernelGGL(k_new_device, dim3(grid), dim3(256), 0, st, h->v, class_id, fs, n, out_handles);
@@ -1277,6 +1343,9 @@ smmo_status smmo_destroy(smmo_heap *h, uint32_t class_id, const uint32_t *handle
     const uint32_t grid = (uint32_t)(((uint64_t)n + 255) / 256);
     hipLaunchKernelGGL(k_destroy, dim3(grid), dim3(256), 0, st, h->v, class_id, handles, n);
     if ((s = launch_check("k_destroy"))) return s;
+    const uint32_t sgrid = std::min((h->v.lvl_n[0] + 3) / 4, 2048u);
+    hipLaunchKernelGGL(k_destroy_settle, dim3(sgrid), dim3(256), 0, st, h->v, class_id);
+    if ((s = launch_check("k_destroy_settle"))) return s;
     h->last = st;
     return SMMO_OK;
 }
