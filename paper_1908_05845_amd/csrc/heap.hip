@@ -139,110 +139,156 @@ __global__ void k_heap_init(HeapView h)
 }
 
 // Enumeration pre-pass (sec.5.2.7 with Alg. indices of sec.5.3.1): compact
-// the set bits of allocated[cls] into R.  Work-group g owns level-0
-// containers 1024 g .. 1024 g + 1023 (thread t loads container 1024 g + t,
-// in the same batch of loads as the error word: the level-1 summary would
-// only add a dependent load, and reading every container costs 8 bytes per
-// 64 blocks).  Each group reserves its ranges of R (dense blocks at the
-// front, sparse ones at the back) and counts itself finished with one 64-bit
-// atomic add on the class's packed counter, so R is ordered within a
-// group's ranges only.  The group whose add finds every other group
-// finished knows the totals: it publishes the lengths and zeroes the
-// counter, so the pass needs no reset launch and can be captured in a
-// graph.  (The lengths are read by later launches only, after every group's
-// appends have been performed.)
+// the set bits of allocated[cls] into R.  A wavefront takes kPer containers
+// of level 0, a work-group the 16 kPer of its wavefronts (every container is
+// read: the level-1 summary would only add a dependent load for 8 bytes per
+// 64 blocks).  A lane takes one block of a container, so bitmaps are read and
+// R is written in runs.  The packing plan (split): blocks with more than 32
+// live objects are dense.  Without it every block counts as dense.
+// The work-group's place in R:
+//   in order    (at most 1,024 containers) it counts the blocks of the
+//               work-groups before it itself, from all the containers, one a
+//               thread; for a plan also from their blocks' bitmaps.  R is in
+//               block order, and nothing is shared between work-groups.
+//   as it comes it reserves its ranges (dense blocks at the front, sparse
+//               ones at the back) and counts itself finished with one 64-bit
+//               atomic add on the class's packed counter, so R is ordered
+//               within a work-group's ranges only.  The work-group whose add
+//               finds every other one finished knows the totals: it publishes
+//               the lengths and zeroes the counter, so the pass needs no
+//               reset launch and can be captured in a graph.
+// (The lengths are read by later launches only.)
+// Bound by its chain of dependent accesses and the launch, as long as there
+// are work-groups for the CUs: with 1,024 containers a work-group, a thread
+// writing the entries of each, one CU wrote what 65,536 blocks list.  A full
+// list of 294,000 blocks 50 us, 7.6 now; wa-tor on 1024 x 1024 cells 9 and
+// 5.3.  With snapshot and plan, launch included, 65,536 full blocks 53 us and
+// 11, 1M 59 and 14, 4M 59 and 20, 16M 60 and 49; 4,096 15 and 10.5.
 constexpr uint64_t kPackMask = (1ull << 25) - 1;
+constexpr uint32_t kFewContainers = 1024;     // in order: one container a thread
+constexpr uint32_t kManyContainers = 16384;   // beyond: 16 containers a wavefront, for the atomics' sake
 static_assert(kMaxBlocks <= kPackMask, "block counts must fit the packed enumeration counter");
-static_assert((kMaxBlocks / 64 + 1024) / 1024 < (1u << 14), "work-group counts must fit the packed enumeration counter");
+static_assert((kMaxBlocks / 64 + 256) / 256 < (1u << 14) && kManyContainers / 64 < (1u << 14),
+              "work-group counts must fit the packed enumeration counter");
 
-__global__ __launch_bounds__(1024) void k_enumerate(HeapView h, uint32_t cls, uint32_t snapshot, uint32_t split)
+template <int kPer>
+__global__ __launch_bounds__(1024) void k_enumerate(HeapView h, uint32_t cls, uint32_t snapshot, uint32_t split,
+                                                    uint32_t ordered)
 {
-    const uint32_t lane = lane_id();
-    const uint32_t wig = threadIdx.x >> 6;
+    constexpr int kBatch = kPer < 8 ? kPer : 8;
+    constexpr uint32_t kGroup = 16 * kPer;
+    __shared__ uint64_t s_c[kGroup], s_d[kGroup];
+    __shared__ uint64_t s_all[kFewContainers];
+    __shared__ uint32_t s_nd[16], s_ns[16], s_bd[16], s_bs[16];
+    __shared__ uint32_t s_kd, s_ks;
+    const uint32_t lane = lane_id(), wig = threadIdx.x >> 6;
     const uint32_t n0 = h.lvl_n[0];
-    const uint32_t cidx = blockIdx.x * 1024 + threadIdx.x;
-    const uint32_t err = ald32(h.ctrl + CTRL_ERR);
-    uint64_t c = cidx < n0 ? ald(h.bm_word(bm_alloc(cls), 0, cidx)) : 0ull;
-    if (err) c = 0;       // a failed heap lists nothing
-    // The packing plan (split): blocks with more than 32 live objects are
-    // dense.  Without it every block counts as dense.  No wavefront changes
-    // a bitmap while this kernel runs, so plain loads are enough.  The
-    // per-block work (the snapshot copy, the plan) is spread over the
-    // work-group: container j of the group's 1,024 goes to wave j mod 16,
-    // one block per lane, so a lane issues its (at most 64) bitmap loads
-    // eight at a time, independent of each other, instead of following one
-    // container's set bits in a chain of dependent loads.
-    __shared__ uint64_t s_c[1024], s_d[1024];
-    __shared__ uint32_t s_nd[16], s_ns[16];
-    __shared__ uint64_t s_old;
-    uint64_t dense = c;
-    if (snapshot || split) {
-        s_c[threadIdx.x] = c;
-        s_d[threadIdx.x] = 0;
-        __syncthreads();
-        const uint64_t gbase = (uint64_t)blockIdx.x * 1024 * 64;   // first block of the group
-        const uint64_t *abm = h.alloc_bm + gbase;
-        uint64_t *ibm = h.iter_bm + gbase;
-        for (uint32_t j0 = wig; j0 < 1024; j0 += 128) {
-            uint64_t cw[8], bm[8];
-            uint64_t any = 0;
+    const uint32_t base = blockIdx.x * kGroup;
+    const uint64_t *const C = h.bm_word(bm_alloc(cls), 0, 0);
+    const bool ok = ald32(h.ctrl + CTRL_ERR) == 0;       // a failed heap lists nothing
+    // No wavefront changes a bitmap while this kernel runs, so plain loads
+    // are enough.
+    const uint64_t mine = ok && ordered && threadIdx.x < n0 ? C[threadIdx.x] : 0ull;
+
+    uint32_t nd = 0, ns = 0;
+    for (int u0 = 0; u0 < kPer; u0 += kBatch) {
+        const uint32_t j0 = wig * kPer + u0;
+        uint64_t c[kBatch], bm[kBatch];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                cw[u] = s_c[j0 + 16 * u];
-                any |= cw[u];
-            }
-            if (!any) continue;
+        for (int u = 0; u < kBatch; ++u) c[u] = ok && base + j0 + u < n0 ? uniform64(C[base + j0 + u]) : 0ull;
 #pragma unroll
-            for (int u = 0; u < 8; ++u)
-                bm[u] = ((cw[u] >> lane) & 1) ? abm[(uint64_t)(j0 + 16 * u) * 64 + lane] : 0ull;
+        for (int u = 0; u < kBatch; ++u)
+            bm[u] = (snapshot | split) && ((c[u] >> lane) & 1) ? h.alloc_bm[(uint64_t)(base + j0 + u) * 64 + lane] : 0ull;
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const bool in = (cw[u] >> lane) & 1;
-                if (snapshot && in) ibm[(uint64_t)(j0 + 16 * u) * 64 + lane] = bm[u];
-                const uint64_t d = __ballot(in && (!split || __popcll(bm[u]) > 32));
-                if (lane == 0) s_d[j0 + 16 * u] = d;
+        for (int u = 0; u < kBatch; ++u) {
+            const bool in = (c[u] >> lane) & 1;
+            if (snapshot && in) h.iter_bm[(uint64_t)(base + j0 + u) * 64 + lane] = bm[u];
+            const uint64_t d = split ? __ballot(in && __popcll(bm[u]) > 32) : c[u];
+            nd += (uint32_t)__popcll(d);
+            ns += (uint32_t)__popcll(c[u] & ~d);
+            if (lane == 0) {
+                s_c[j0 + u] = c[u];
+                s_d[j0 + u] = d;
             }
         }
-        __syncthreads();
-        dense = s_d[threadIdx.x];
     }
-    const uint32_t nd = (uint32_t)__popcll(dense), ns = (uint32_t)__popcll(c) - nd;
-    const uint32_t incl_d = wave_incl_scan(nd), incl_s = wave_incl_scan(ns);
-    if (lane == 63) {
-        s_nd[wig] = incl_d;
-        s_ns[wig] = incl_s;
+    uint32_t bd = 0, bs = 0;                             // of the work-groups before this one
+    if (ordered) {
+        if (split) {
+            s_all[threadIdx.x] = mine;
+            __syncthreads();
+            for (uint32_t j0 = wig; j0 < base; j0 += 256) {
+                uint64_t c[16], bm[16];
+#pragma unroll
+                for (int u = 0; u < 16; ++u) c[u] = j0 + 16 * u < base ? s_all[j0 + 16 * u] : 0ull;
+#pragma unroll
+                for (int u = 0; u < 16; ++u)
+                    bm[u] = (c[u] >> lane) & 1 ? h.alloc_bm[(uint64_t)(j0 + 16 * u) * 64 + lane] : 0ull;
+#pragma unroll
+                for (int u = 0; u < 16; ++u) {
+                    const uint32_t d = (uint32_t)__popcll(__ballot(__popcll(bm[u]) > 32));
+                    bd += d;
+                    bs += (uint32_t)__popcll(c[u]) - d;
+                }
+            }
+        } else {
+            uint32_t k = threadIdx.x < base ? (uint32_t)__popcll(mine) : 0u;
+#pragma unroll
+            for (int d = 1; d < 64; d <<= 1) k += (uint32_t)__shfl_xor((int)k, d);
+            bd = k;
+        }
+    }
+    if (lane == 0) {
+        s_nd[wig] = nd;
+        s_ns[wig] = ns;
+        s_bd[wig] = bd;
+        s_bs[wig] = bs;
     }
     __syncthreads();
     if (threadIdx.x == 0) {
-        uint32_t td = 0, ts = 0;
+        uint32_t td = 0, ts = 0, kd = 0, ks = 0;
         for (int k = 0; k < 16; ++k) {
             td += s_nd[k];
             ts += s_ns[k];
+            kd += s_bd[k];
+            ks += s_bs[k];
         }
-        const uint64_t add = (uint64_t)td | ((uint64_t)ts << 25) | (1ull << 50);
+        bool last;
         uint64_t *pack = reinterpret_cast<uint64_t *>(h.ctrl + CTRL_RPACK + 2 * cls);
-        const uint64_t old = __hip_atomic_fetch_add(pack, add, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        s_old = old;
-        if ((old >> 50) == gridDim.x - 1) {
-            const uint64_t tot = old + add;
-            const uint32_t rd = (uint32_t)(tot & kPackMask), rs = (uint32_t)((tot >> 25) & kPackMask);
-            __hip_atomic_store(h.ctrl + CTRL_RFINAL + cls, rd + rs, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            __hip_atomic_store(h.ctrl + CTRL_RSFINAL + cls, rs, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            __hip_atomic_store(pack, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (ordered) {
+            last = blockIdx.x == gridDim.x - 1;
+        } else {
+            const uint64_t add = (uint64_t)td | ((uint64_t)ts << 25) | (1ull << 50);
+            const uint64_t old = __hip_atomic_fetch_add(pack, add, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            kd = (uint32_t)(old & kPackMask);
+            ks = (uint32_t)((old >> 25) & kPackMask);
+            last = (old >> 50) == gridDim.x - 1;
+            if (last) __hip_atomic_store(pack, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
+        if (last) {
+            __hip_atomic_store(h.ctrl + CTRL_RFINAL + cls, kd + td + ks + ts, __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(h.ctrl + CTRL_RSFINAL + cls, ks + ts, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        s_kd = kd;
+        s_ks = ks;
     }
     __syncthreads();
-    const uint64_t old = s_old;
-    uint32_t kd = (uint32_t)(old & kPackMask) + incl_d - nd, ks = (uint32_t)((old >> 25) & kPackMask) + incl_s - ns;
+    uint32_t kd = s_kd, ks = s_ks;
     for (uint32_t k = 0; k < wig; ++k) {      // the ranges of the group's earlier wavefronts
         kd += s_nd[k];
         ks += s_ns[k];
     }
     uint32_t *R = h.R + (uint64_t)cls * h.M;
-    for (; c; c &= c - 1) {
-        const uint32_t b = (uint32_t)(__ffsll((unsigned long long)c) - 1);
-        if ((dense >> b) & 1) R[kd++] = cidx * 64 + b;
-        else R[h.M - 1 - ks++] = cidx * 64 + b;
+    const uint64_t below = (1ull << lane) - 1;
+#pragma unroll 4
+    for (uint32_t j = wig * kPer; j < (wig + 1) * kPer; ++j) {
+        const uint64_t c = uniform64(s_c[j]), d = uniform64(s_d[j]), sp = c & ~d;
+        const uint32_t b = (base + j) * 64 + lane;
+        if ((d >> lane) & 1) R[kd + (uint32_t)__popcll(d & below)] = b;
+        else if ((sp >> lane) & 1) R[h.M - 1 - (ks + (uint32_t)__popcll(sp & below))] = b;
+        kd += (uint32_t)__popcll(d);
+        ks += (uint32_t)__popcll(sp);
     }
 }
 
@@ -824,7 +870,7 @@ int &list_state(smmo_heap *h, uint32_t cls, hipStream_t st)
 } // namespace
 
 smmo_status ensure_enumerated(smmo_heap *h, uint32_t cls, bool snapshot, hipStream_t st, bool split,
-                              bool allow_direct)
+                              bool allow_direct, bool in_order)
 {
     // a do-all that uses a snapshot from smmo_snapshot walks that list as it is
     if ((h->v.snap >> cls) & 1) return SMMO_OK;
@@ -844,10 +890,15 @@ smmo_status ensure_enumerated(smmo_heap *h, uint32_t cls, bool snapshot, hipStre
     }
     h->v.direct &= ~(1u << cls);
     h->snap_pending &= ~(1u << cls);     // the list is rebuilt: a snapshot taken before is gone
-    const uint32_t nwaves = (h->v.lvl_n[0] + 63) / 64;
-    const uint32_t grid = (nwaves + 15) / 16;
-    hipLaunchKernelGGL(k_enumerate, dim3(grid), dim3(1024), 0, st, h->v, cls, snapshot ? 1u : 0u,
-                       split ? 1u : 0u);
+    // In block order where a work-group can count what lies before it.  For a
+    // plan that costs a read of those blocks' bitmaps, and only the walks of a
+    // snapshot that smmo_snapshot takes may depend on the order: any method
+    // can use it, a packed one of its own visits objects in no order.
+    const uint32_t n0 = h->v.lvl_n[0];
+    const uint32_t ordered = n0 <= kFewContainers && (!split || in_order) ? 1u : 0u;
+    const dim3 grid(n0 <= kManyContainers ? (n0 + 63) / 64 : (n0 + 255) / 256);
+    hipLaunchKernelGGL(n0 <= kManyContainers ? k_enumerate<4> : k_enumerate<16>, grid, dim3(1024), 0, st, h->v, cls,
+                       snapshot ? 1u : 0u, split ? 1u : 0u, ordered);
     smmo_status s = launch_check("k_enumerate");
     if (s) return s;
     state = split ? R_SPLIT : R_VALID;
@@ -1305,7 +1356,7 @@ smmo_status smmo_snapshot(smmo_heap *h, uint32_t class_id, smmo_stream stream)
     for (uint32_t c = 0; c < h->schema->nclasses; ++c) {
         if (!((fam >> c) & 1) || class_abstract(h->schema, c)) continue;
         // with the packing plan whenever a packed do-all may ask for it
-        if ((s = ensure_enumerated(h, c, true, st, h->cfg.sparse_packing != 0, false))) return s;
+        if ((s = ensure_enumerated(h, c, true, st, h->cfg.sparse_packing != 0, false, true))) return s;
     }
     h->snap_pending |= fam;
     h->last = st;

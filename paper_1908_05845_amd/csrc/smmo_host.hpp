@@ -125,9 +125,11 @@ smmo_status bind_field(const smmo_schema *s, uint32_t cls, const char *name, int
 // front, sparse ones (at most 32 live objects) at the back (without it every
 // block is listed as dense); allow_direct = a small heap's churning class may
 // be walked over all blocks instead (false: the walk needs the list itself,
-// its positions naming the class's blocks).
+// its positions naming the class's blocks); in_order = a list with a plan, too,
+// is in block order (dense and sparse blocks each) on heaps of at most 65,536
+// blocks, as a list without one always is there.
 smmo_status ensure_enumerated(smmo_heap *h, uint32_t cls, bool snapshot, hipStream_t st, bool split = false,
-                              bool allow_direct = true);
+                              bool allow_direct = true, bool in_order = false);
 
 
 // launch shape of a do-all over class cls: the (method, class) setting of
