@@ -515,9 +515,9 @@ __global__ __launch_bounds__(256) void k_destroy_settle(HeapView h, uint32_t cls
             h.type[bid] = kNull;
             h.alloc_bm[bid] = ~0ull;
         }
-        OpQueue q;
-        q.reset();
         if (lane == 0) {
+            OpQueue q;
+            q.reset();
             *active = some;
             if (!was != !some && h.nlev > 1) q.op[0] = BitOp{c, (uint16_t)bm_active(cls), 1, (int8_t)(some ? 1 : -1)};
             if (empty) {
@@ -528,8 +528,8 @@ __global__ __launch_bounds__(256) void k_destroy_settle(HeapView h, uint32_t cls
                 *free_ = f | empty;
                 if (!f && h.nlev > 1) q.op[2] = BitOp{c, (uint16_t)BM_FREE, 1, 1};
             }
+            run_ops_lane(h, q);
         }
-        run_ops_wave(h, q);
     }
 }
 

@@ -96,6 +96,14 @@ __device__ __forceinline__ bool heap_failed(const HeapView &h)
 // ------------------------------------------------------------ bit helpers --
 __device__ __forceinline__ uint32_t lane_id() { return __lane_id(); }
 
+// lane `from`'s value (from wave-uniform), in scalar registers
+__device__ __forceinline__ uint64_t lane64(uint64_t v, uint32_t from)
+{
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, (int)from);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(v >> 32), (int)from);
+    return ((uint64_t)hi << 32) | lo;
+}
+
 // a value every lane holds alike, moved to scalar registers
 __device__ __forceinline__ uint64_t uniform64(uint64_t v)
 {
@@ -118,6 +126,24 @@ __device__ __forceinline__ uint64_t lowest_bits(uint64_t b, uint32_t n)
     if ((uint32_t)__popcll(b) <= n) return b;
     uint32_t p = nth_set_bit(b, n);   // first bit not taken
     return b & ((1ull << p) - 1);
+}
+
+// the lowest n set bits of a wave-uniform b, n <= 64 (a lane per bit instead of
+// a loop over the bits; converged)
+__device__ __forceinline__ uint64_t wave_lowest_bits(uint64_t b, uint32_t n)
+{
+    const uint32_t lane = lane_id();
+    return __ballot(((b >> lane) & 1) && (uint32_t)__popcll(b & ((1ull << lane) - 1)) < n);
+}
+
+// Lane r of the result is the position of the r-th set bit of a wave-uniform
+// b, for r < popcount(b) (a permutation of the lanes; converged).
+__device__ __forceinline__ uint32_t wave_set_bits(uint64_t b)
+{
+    const uint32_t lane = lane_id();
+    const uint32_t below = (uint32_t)__popcll(b & ((1ull << lane) - 1));
+    const uint32_t to = (b >> lane) & 1 ? below : (uint32_t)__popcll(b) + lane - below;
+    return (uint32_t)__builtin_amdgcn_ds_permute((int)(to << 2), (int)lane);
 }
 
 __device__ __forceinline__ uint32_t hash32(uint32_t x)
@@ -249,8 +275,8 @@ __device__ __forceinline__ void run_ops_wave(const HeapView &h, OpQueue &q)
     }
 }
 
-// The same for a single lane running alone (the allocation leader: no other
-// lane of its wavefront holds pending switches while it runs).
+// The same for a single lane running alone (no other lane of its wavefront
+// holds pending switches while it runs).
 __device__ __forceinline__ void run_ops_lane(const HeapView &h, OpQueue &q)
 {
     if (q.overflow) raise_error(h, ERR_INTERNAL);
@@ -266,12 +292,48 @@ __device__ __forceinline__ void run_ops_lane(const HeapView &h, OpQueue &q)
     }
 }
 
-__device__ __forceinline__ void switch_bit_lane(const HeapView &h, uint32_t bmid, uint32_t pos, int dir)
+// Atomics of an allocating wavefront: made by lane `who`, their results known
+// to every lane (converged).
+__device__ __forceinline__ uint64_t aor_one(uint32_t who, uint64_t *p, uint64_t v)
 {
-    OpQueue q;
-    q.reset();
-    q.push(bmid, pos, dir);
-    run_ops_lane(h, q);
+    uint64_t prev = 0;
+    if (lane_id() == who) prev = aor(p, v);
+    return lane64(prev, who);
+}
+
+__device__ __forceinline__ uint64_t aand_one(uint32_t who, uint64_t *p, uint64_t v)
+{
+    uint64_t prev = 0;
+    if (lane_id() == who) prev = aand(p, v);
+    return lane64(prev, who);
+}
+
+__device__ __forceinline__ void count_event_one(const HeapView &h, uint32_t who, uint32_t ev, uint32_t n = 1)
+{
+    if (lane_id() == who) count_events(h, ev, n);
+}
+
+// Completes one switch, beginning at level lvl, for a wavefront whose lanes
+// hold no other pending switch (converged; all arguments wave-uniform).
+__device__ __forceinline__ void switch_bit_one(const HeapView &h, uint32_t who, uint32_t bmid, uint32_t pos, int dir,
+                                               uint32_t lvl = 0)
+{
+    for (uint32_t it = 0;; ++it) {
+        if (it >= h.spin_limit) {
+            if (lane_id() == who) raise_error(h, ERR_SPIN);
+            return;
+        }
+        uint64_t *const w = h.bm_word(bmid, lvl, pos >> 6);
+        const uint64_t bit = 1ull << (pos & 63);
+        const uint64_t prev = dir > 0 ? aor_one(who, w, bit) : aand_one(who, w, ~bit);
+        const bool was = (prev & bit) != 0;
+        if (was != (dir > 0)) {                      // switched here
+            if ((dir > 0 ? prev != 0 : prev != bit) || lvl + 1 >= h.nlev) return;
+            ++lvl;
+            pos >>= 6;
+        }
+        count_event_one(h, who, EV_SPIN);
+    }
 }
 
 // The set bit of container c != 0 that a search at level lvl takes: the first
@@ -301,52 +363,49 @@ __device__ __forceinline__ uint32_t pick_bit(const HeapView &h, uint64_t c, uint
 // full containers did: 4096 x 4096 cells took 2.5 ms a generation (3.3 M of
 // 10.2 M searches wasted over twelve), 0.74 ms now (0.3 M of 4.2 M); 256 x 256
 // cells 29 us before both changes, 21.5 us now.
-__device__ __forceinline__ int64_t find_set(const HeapView &h, uint32_t bmid, uint32_t seed)
+// Converged call, every argument and the result wave-uniform.
+__device__ __forceinline__ uint32_t find_set(const HeapView &h, uint32_t who, uint32_t bmid, uint32_t seed)
 {
-    count_event(h, EV_FIND);
+    count_event_one(h, who, EV_FIND);
     uint32_t idx = 0;
     for (int lvl = (int)h.nlev - 1; lvl >= 0; --lvl) {
-        const uint64_t c = ald(h.bm_word(bmid, (uint32_t)lvl, idx));
-        if (!c) return -1;
+        const uint64_t c = uniform64(ald(h.bm_word(bmid, (uint32_t)lvl, idx)));
+        if (!c) return kNoBlock;
         const uint32_t b = bmid == BM_FREE && lvl >= 2 ? (uint32_t)(__ffsll((unsigned long long)c) - 1)
                                                        : pick_bit(h, c, seed, (uint32_t)lvl);
         idx = idx * 64u + b;
     }
-    return (int64_t)idx;
+    return idx;
 }
 
 // Bitmap::clear() on the free-block bitmap: find a set bit and switch it off;
-// retry the search if another thread switched it first.  Returns -1 when no
-// free block is found (the thesis spins forever here; we report exhaustion).
-__device__ __forceinline__ int64_t claim_free_block(const HeapView &h, uint32_t seed)
+// retry the search if another thread switched it first.  Returns kNoBlock when
+// no free block is found (the thesis spins forever here; we report exhaustion).
+// Converged call, wave-uniform as find_set.
+__device__ __forceinline__ uint32_t claim_free_block(const HeapView &h, uint32_t who, uint32_t seed)
 {
     uint32_t misses = 0;
     for (uint32_t t = 0; t < h.spin_limit; ++t) {
-        const int64_t b = find_set(h, BM_FREE, seed + t * 0x632BE5ABu);
-        if (b < 0) {
+        const uint32_t b = find_set(h, who, BM_FREE, seed + t * 0x632BE5ABu);
+        if (b == kNoBlock) {
             // A search can miss while another thread is between two levels
             // of the hierarchy; only a run of consecutive misses means the
             // heap is exhausted.  Races lost to other claimers (below) are
             // progress of others and do not count.
-            if (++misses > 128u) return -1;
+            if (++misses > 128u) return kNoBlock;
             __builtin_amdgcn_s_sleep(4);
             continue;
         }
         misses = 0;
-        uint64_t *w = h.bm_word(BM_FREE, 0, (uint32_t)b >> 6);
         const uint64_t bit = 1ull << (b & 63);
-        const uint64_t prev = aand(w, ~bit);
+        const uint64_t prev = aand_one(who, h.bm_word(BM_FREE, 0, b >> 6), ~bit);
         if (!(prev & bit)) continue;           // someone else took it
-        if (prev == bit && h.nlev > 1) {        // cleared the container's last bit
-            OpQueue q;
-            q.reset();
-            q.op[0] = BitOp{(uint32_t)b >> 6, (uint16_t)BM_FREE, 1, -1};
-            run_ops_lane(h, q);
-        }
+        if (prev == bit && h.nlev > 1)         // cleared the container's last bit
+            switch_bit_one(h, who, BM_FREE, b >> 6, -1, 1);
         return b;
     }
-    raise_error(h, ERR_SPIN);
-    return -1;
+    if (lane_id() == who) raise_error(h, ERR_SPIN);
+    return kNoBlock;
 }
 
 // Alg. initialize_block: publish the type, then reset the allocation bitmap
@@ -362,17 +421,18 @@ __device__ __forceinline__ void initialize_block(const HeapView &h, uint32_t bid
 
 // Block::reserve, extended to up to n slots at once (reserve_multiple):
 // returns the mask of slots this call switched 0 -> 1 (0 = block full or
-// invalidated) and whether this call made the block full.
-__device__ __forceinline__ uint64_t reserve_slots(const HeapView &h, uint32_t bid, uint32_t n,
+// invalidated) and whether this call made the block full.  Converged call,
+// wave-uniform as find_set.
+__device__ __forceinline__ uint64_t reserve_slots(const HeapView &h, uint32_t who, uint32_t bid, uint32_t n,
                                                   bool &filled)
 {
     uint64_t *p = h.alloc_bm + bid;
-    uint64_t cur = ald(p);
+    uint64_t cur = uniform64(ald(p));
     filled = false;
     for (int it = 0; it < 64; ++it) {
-        const uint64_t want = lowest_bits(~cur, n);
+        const uint64_t want = wave_lowest_bits(~cur, n);
         if (!want) return 0;
-        const uint64_t prev = aor(p, want);
+        const uint64_t prev = aor_one(who, p, want);
         const uint64_t got = want & ~prev;
         if (got) {
             filled = (prev | want) == ~0ull;
@@ -441,51 +501,91 @@ __device__ __forceinline__ void release_slots(const HeapView &h, uint32_t cls, u
 }
 
 // ------------------------------------------------------------- allocation --
+// release_slots (and invalidate_block) for a wavefront that gives back slots of
+// one block: the same steps, each switch completed before the next.  A switch only ever waits for one that an
+// earlier change of its block's bitmap calls for, and a wavefront makes its
+// own in the order of its changes, so no two can wait for each other.
+// (Without a queue, which in the middle of an allocation costs 36 registers.)
+__device__ __forceinline__ void give_back_slots(const HeapView &h, uint32_t who, uint32_t cls, uint32_t bid,
+                                                uint64_t mask)
+{
+    uint64_t *const p = h.alloc_bm + bid;
+    const uint64_t prev = aand_one(who, p, ~mask);
+    if ((prev & mask) != mask) {
+        if (lane_id() == who) raise_error(h, ERR_BADHANDLE);
+        return;
+    }
+    count_event_one(h, who, EV_DELS, (uint32_t)__popcll(mask));
+    if (prev == ~0ull) switch_bit_one(h, who, bm_active(cls), bid, +1);
+    if ((prev & ~mask) != 0) return;
+    for (int attempt = 0; attempt < kInvalidateAttempts; ++attempt) {
+        const uint64_t before = aor_one(who, p, ~0ull);
+        if (before == ~0ull) return;
+        const uint32_t t = (uint32_t)__builtin_amdgcn_readfirstlane((int)ald32(h.type + bid));
+        if (before == 0) {
+            if (lane_id() == who)
+                __hip_atomic_store(h.type + bid, kNull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            complete_prior();
+            switch_bit_one(h, who, bm_active(t), bid, -1);
+            switch_bit_one(h, who, bm_alloc(t), bid, -1);
+            switch_bit_one(h, who, BM_FREE, bid, +1);
+            return;
+        }
+        const uint64_t before_rb = aand_one(who, p, before);
+        if (before_rb != ~0ull) switch_bit_one(h, who, bm_active(t), bid, -1);
+        if ((before_rb & before) != 0) return;
+    }
+}
+
 // The leader's part of Alg. allocate with request coalescing: find an active
 // block of the class (lookup retry with rotation), else initialize a free
 // block (slow path); reserve up to n slots; deactivate the block if this
 // filled it; roll back if the block's type changed meanwhile.
-__device__ __forceinline__ uint32_t leader_allocate(const HeapView &h, uint32_t cls, uint32_t n,
-                                                    uint64_t &got, uint32_t seed, int64_t first = -1)
+// The whole wavefront runs it, with wave-uniform values in scalar registers;
+// lane `who` makes the atomics.  Run by that lane alone, its values were in
+// vector registers, 104 of them in a kernel that allocates: four wavefronts a
+// SIMD, where an allocation, a chain of dependent accesses, wants as many in
+// flight as there can be.  69 and seven now: death and birth of a generation of
+// 4096 x 4096 cells 600 us before, 457 so, 401 with the deaths' releases made
+// the same way; births of 256 x 256 cells 14.3 us and 12.5.
+__device__ __forceinline__ uint32_t leader_allocate(const HeapView &h, uint32_t who, uint32_t cls, uint32_t n,
+                                                    uint64_t &got, uint32_t seed, uint32_t first = kNoBlock)
 {
     got = 0;
     for (uint32_t attempt = 0; attempt < h.spin_limit; ++attempt) {
         // the first attempt may start from a block found in a prefetched
         // view of the active bitmap (wave_allocate with an ActiveView)
-        int64_t bid = attempt == 0 ? first : -1;
-        for (uint32_t t = 0; t < h.retries && bid < 0; ++t)
-            bid = find_set(h, bm_active(cls), hash32(seed + attempt * 977u + t * 131u));
-        if (bid < 0) {
-            bid = claim_free_block(h, hash32(seed ^ (attempt * 0x27d4eb2fu)));
-            if (bid < 0) {
-                raise_error(h, ERR_NOMEM);
+        uint32_t bid = attempt == 0 ? first : kNoBlock;
+        for (uint32_t t = 0; t < h.retries && bid == kNoBlock; ++t)
+            bid = find_set(h, who, bm_active(cls), hash32(seed + attempt * 977u + t * 131u));
+        if (bid == kNoBlock) {
+            bid = claim_free_block(h, who, hash32(seed ^ (attempt * 0x27d4eb2fu)));
+            if (bid == kNoBlock) {
+                if (lane_id() == who) raise_error(h, ERR_NOMEM);
                 return kNoBlock;
             }
-            initialize_block(h, (uint32_t)bid, cls);
-            switch_bit_lane(h, bm_alloc(cls), (uint32_t)bid, +1);
-            switch_bit_lane(h, bm_active(cls), (uint32_t)bid, +1);
-            count_event(h, EV_SLOW);
+            if (lane_id() == who) initialize_block(h, bid, cls);
+            switch_bit_one(h, who, bm_alloc(cls), bid, +1);
+            switch_bit_one(h, who, bm_active(cls), bid, +1);
+            count_event_one(h, who, EV_SLOW);
         }
         bool filled;
-        const uint64_t g = reserve_slots(h, (uint32_t)bid, n, filled);
+        const uint64_t g = reserve_slots(h, who, bid, n, filled);
         if (g) {
             // issued after the reservation has been performed (its result
             // is used), so it sees the type published before the reset
-            const uint32_t t = ald32(h.type + bid);
-            if (filled) switch_bit_lane(h, bm_active(t), (uint32_t)bid, -1);
+            const uint32_t t = __builtin_amdgcn_readfirstlane(ald32(h.type + bid));
+            if (filled) switch_bit_one(h, who, bm_active(t), bid, -1);
             if (t == cls) {
                 got = g;
-                count_events(h, EV_NEWS, (uint64_t)__popcll(g));
-                return (uint32_t)bid;
+                count_event_one(h, who, EV_NEWS, (uint32_t)__popcll(g));
+                return bid;
             }
-            OpQueue q;                     // block re-typed meanwhile: roll back
-            q.reset();
-            release_slots(h, t, (uint32_t)bid, g, q);
-            run_ops_lane(h, q);
+            give_back_slots(h, who, t, bid, g);   // block re-typed meanwhile: roll back
         }
-        count_event(h, EV_RETRY);
+        count_event_one(h, who, EV_RETRY);
     }
-    raise_error(h, ERR_SPIN);
+    if (lane_id() == who) raise_error(h, ERR_SPIN);
     return kNoBlock;
 }
 
@@ -512,25 +612,23 @@ __device__ __forceinline__ ActiveView active_view(const HeapView &h, uint32_t cl
 
 // The rest of Alg. try_find_set from a view: the container at level L and the
 // bit in it picked as find_set picks them, then the levels below L by loads.  Converged call; the result is
-// wave-uniform (-1 if the view shows no active block).
-__device__ __forceinline__ int64_t find_set_from_view(const HeapView &h, uint32_t bmid, const ActiveView &v,
+// wave-uniform (kNoBlock if the view shows no active block).
+__device__ __forceinline__ uint32_t find_set_from_view(const HeapView &h, uint32_t bmid, const ActiveView &v,
                                                       uint32_t seed)
 {
     const int lvl = h.nlev >= 2 ? (int)h.nlev - 2 : 0;
     const uint64_t nz = __ballot(v.w != 0);
-    if (!nz) return -1;
+    if (!nz) return kNoBlock;
     uint32_t idx = 0;
     if (h.nlev >= 2) idx = pick_bit(h, nz, seed, (uint32_t)lvl + 1);   // the single container above L, as the ballot
-    const uint32_t lo = (uint32_t)__shfl((int)(uint32_t)v.w, (int)idx);
-    const uint32_t hi = (uint32_t)__shfl((int)(uint32_t)(v.w >> 32), (int)idx);
-    uint64_t c = ((uint64_t)hi << 32) | lo;
+    uint64_t c = lane64(v.w, idx);
     for (int l = lvl;; --l) {
         idx = idx * 64u + pick_bit(h, c, seed, (uint32_t)l);
         if (l == 0) break;
         c = uniform64(ald(h.bm_word(bmid, (uint32_t)l - 1, idx)));
-        if (!c) return -1;
+        if (!c) return kNoBlock;
     }
-    return (int64_t)idx;
+    return idx;
 }
 
 // Allocation of one object of class `cls` for every lane with want = true.
@@ -545,32 +643,29 @@ __device__ __forceinline__ uint32_t wave_allocate(const HeapView &h, uint32_t cl
     uint32_t result = kNull;
     uint64_t pending = __ballot(want);
     const uint32_t lane = lane_id();
-    const uint32_t seed = hash32(global_wave_id() * 0x9E3779B1u + 0x51ED27u);
+    const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)global_wave_id());
+    const uint32_t seed = hash32(wave * 0x9E3779B1u + 0x51ED27u);
     for (uint32_t round = 0; pending; ++round) {
         const uint32_t leader = (uint32_t)(__ffsll((unsigned long long)pending) - 1);
         const uint32_t n = h.coalescing ? (uint32_t)__popcll(pending) : 1u;
-        uint32_t bid = kNoBlock;
-        uint64_t got = 0;
+        uint64_t got;
         const uint32_t rseed = seed + round * 0x85ebca6bu;
         // the first round's first lookup from the view (seeded as the
         // ordinary search's first lookup would be)
-        int64_t first = -1;
+        uint32_t first = kNoBlock;
         if (view && round == 0) {
-            if (lane == leader) count_event(h, EV_FIND);
+            count_event_one(h, leader, EV_FIND);
             first = find_set_from_view(h, bm_active(cls), *view, hash32(rseed));
         }
-        if (lane == leader) bid = leader_allocate(h, cls, n, got, rseed, first);
-        bid = __shfl(bid, (int)leader);
-        const uint32_t glo = __shfl((uint32_t)got, (int)leader);
-        const uint32_t ghi = __shfl((uint32_t)(got >> 32), (int)leader);
-        got = ((uint64_t)ghi << 32) | glo;
+        const uint32_t bid = leader_allocate(h, leader, cls, n, got, rseed, first);
         if (bid == kNoBlock) break;
         const uint32_t k = (uint32_t)__popcll(got);
-        if ((pending >> lane) & 1) {
-            const uint32_t rank = (uint32_t)__popcll(pending & ((1ull << lane) - 1));
-            if (rank < k) result = (bid << 6) | nth_set_bit(got, rank);
-        }
-        pending &= ~lowest_bits(pending, k);
+        // the lane of rank r takes the r-th reserved slot
+        const uint32_t rank = (uint32_t)__popcll(pending & ((1ull << lane) - 1));
+        const uint32_t slot = (uint32_t)__builtin_amdgcn_ds_bpermute((int)((rank & 63) << 2), (int)wave_set_bits(got));
+        const bool served = ((pending >> lane) & 1) && rank < k;
+        if (served) result = (bid << 6) | slot;
+        pending &= ~__ballot(served);
     }
     return result;
 }
@@ -651,15 +746,14 @@ __device__ __forceinline__ void wave_deallocate(const HeapView &h, uint32_t cls,
 // wavefront processes one block, so all its releases go to that block and
 // are combined into one atomic (the multi-slot release of sec.5.3.2).
 // Converged call; `mask` is the ballot of the lanes deleting their object.
+// One release at a time, as an allocating wavefront gives slots back: 24 vector
+// registers for Alive::death where the queue took 59.
 __device__ __forceinline__ void wave_release_own_block(const HeapView &h, uint32_t cls, uint32_t bid,
                                                        uint64_t mask)
 {
     if (!mask) return;
-    OpQueue q;
-    q.reset();
-    const uint32_t leader = (uint32_t)(__ffsll((unsigned long long)mask) - 1);
-    if (lane_id() == leader) release_slots(h, cls, bid, mask, q);
-    run_ops_wave(h, q);
+    give_back_slots(h, (uint32_t)(__ffsll((unsigned long long)mask) - 1), cls,
+                    (uint32_t)__builtin_amdgcn_readfirstlane((int)bid), mask);
 }
 
 } // namespace smmo
