@@ -495,7 +495,7 @@ __global__ __launch_bounds__(256) void k_destroy(HeapView h, uint32_t cls, const
 
 // Second launch: brings the states of the class's blocks in line with their
 // slots, 64 blocks of one container a wavefront.  A block without objects
-// becomes free (its type unset, its slots all taken, as invalidate_block
+// becomes free (its type unset, its slots all taken, as a release
 // leaves it), one with free slots active.  Nothing else runs on the heap, so
 // a container is its wavefront's own; what passes on to the next levels goes
 // through the switches that other wavefronts' containers meet there.

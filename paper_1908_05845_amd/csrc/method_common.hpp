@@ -253,10 +253,8 @@ __device__ __forceinline__ void wave_release_packed(const HeapView &h, uint32_t 
         hi |= (uint32_t)__shfl_xor((int)hi, d);
     }
     const uint64_t mask = ((uint64_t)hi << 32) | lo;
-    OpQueue q;
-    q.reset();
-    if ((lane_id() & 31) == 0 && mask) release_slots(h, cls, bid, mask, q);
-    run_ops_wave(h, q);
+    const uint64_t mine = (lane_id() & 31) == 0 ? mask : 0;
+    if (release_beside(h, cls, bid, mine)) count_events(h, EV_DELS, (uint64_t)__popcll(mine));
 }
 
 template <class T>

@@ -443,69 +443,20 @@ __device__ __forceinline__ uint64_t reserve_slots(const HeapView &h, uint32_t wh
     return 0;
 }
 
-// Alg. invalidate: try to switch all 64 slots to 1 so that no reservation can
-// succeed; on success the block is empty and can be freed; if some slot was
-// reserved meanwhile, roll back (and owe the deferred active-bit clear when a
-// concurrent release saw the block as full).  Bitmap switches are queued,
-// not performed, so that the caller can complete them in a converged loop.
-// Returns true if the block was invalidated.
-__device__ __forceinline__ bool invalidate_block(const HeapView &h, uint32_t bid, OpQueue &q)
-{
-    uint64_t *p = h.alloc_bm + bid;
-    for (int attempt = 0; attempt < kInvalidateAttempts; ++attempt) {
-        const uint64_t before = aor(p, ~0ull);
-        if (before == ~0ull) return false;
-        const uint32_t t = ald32(h.type + bid);
-        if (before == 0) {
-            // The block is ours and empty.  Retire its type before it is
-            // marked free, so a stale block list sees it as not of class t
-            // and a later initialize_block's store of a new type comes after.
-            __hip_atomic_store(h.type + bid, kNull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            complete_prior();
-            q.push(bm_active(t), bid, -1);
-            q.push(bm_alloc(t), bid, -1);
-            q.push(BM_FREE, bid, +1);
-            return true;
-        }
-        const uint64_t before_rb = aand(p, before);
-        if (before_rb != ~0ull) q.push(bm_active(t), bid, -1);
-        if ((before_rb & before) != 0) return false;
-        // empty again: retry the invalidation
-    }
-    return false;
-}
-
+// ------------------------------------------------------------- allocation --
 // Block::deallocate for a set of slots of one block, with the block-state
 // consequences of Alg. deallocate: the release that frees the first slot of a
-// full block re-activates it; the release that empties it invalidates it.
-// Switches are queued into q.  Returns whether the slots were live (the
-// caller counts the deletions); releasing a free slot raises the bad-handle
-// error.
-__device__ __forceinline__ bool release_slots_uncounted(const HeapView &h, uint32_t cls, uint32_t bid,
-                                                        uint64_t mask, OpQueue &q)
-{
-    const uint64_t prev = aand(h.alloc_bm + bid, ~mask);
-    if ((prev & mask) != mask) {
-        raise_error(h, ERR_BADHANDLE);
-        return false;
-    }
-    if (prev == ~0ull) q.push(bm_active(cls), bid, +1);
-    if ((prev & ~mask) == 0) invalidate_block(h, bid, q);
-    return true;
-}
+// full block re-activates it; the release that empties it invalidates it (Alg.
+// invalidate: try to switch all 64 slots to 1 so that no reservation can
+// succeed; on success the block is empty and can be freed; if some slot was
+// reserved meanwhile, roll back, and owe the deferred active-bit clear when a
+// concurrent release saw the block as full).  Releasing a free slot raises the
+// bad-handle error.  Each switch is completed before the next is begun: one
+// only ever waits for a switch that an earlier change of its block's bitmap
+// calls for, and every wavefront makes its own in the order of its changes, so
+// no two can wait for each other.
 
-__device__ __forceinline__ void release_slots(const HeapView &h, uint32_t cls, uint32_t bid,
-                                              uint64_t mask, OpQueue &q)
-{
-    if (release_slots_uncounted(h, cls, bid, mask, q)) count_events(h, EV_DELS, (uint64_t)__popcll(mask));
-}
-
-// ------------------------------------------------------------- allocation --
-// release_slots (and invalidate_block) for a wavefront that gives back slots of
-// one block: the same steps, each switch completed before the next.  A switch only ever waits for one that an
-// earlier change of its block's bitmap calls for, and a wavefront makes its
-// own in the order of its changes, so no two can wait for each other.
-// (Without a queue, which in the middle of an allocation costs 36 registers.)
+// ... for one block, by lane `who` (converged, arguments wave-uniform).
 __device__ __forceinline__ void give_back_slots(const HeapView &h, uint32_t who, uint32_t cls, uint32_t bid,
                                                 uint64_t mask)
 {
@@ -523,6 +474,9 @@ __device__ __forceinline__ void give_back_slots(const HeapView &h, uint32_t who,
         if (before == ~0ull) return;
         const uint32_t t = (uint32_t)__builtin_amdgcn_readfirstlane((int)ald32(h.type + bid));
         if (before == 0) {
+            // The block is ours and empty.  Retire its type before it is
+            // marked free, so a stale block list sees it as not of class t
+            // and a later initialize_block's store of a new type comes after.
             if (lane_id() == who)
                 __hip_atomic_store(h.type + bid, kNull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             complete_prior();
@@ -534,7 +488,75 @@ __device__ __forceinline__ void give_back_slots(const HeapView &h, uint32_t who,
         const uint64_t before_rb = aand_one(who, p, before);
         if (before_rb != ~0ull) switch_bit_one(h, who, bm_active(t), bid, -1);
         if ((before_rb & before) != 0) return;
+        // empty again: retry the invalidation
     }
+}
+
+// One switch a lane, where todo, completed by all of them together (converged;
+// the lanes' switches go the same way in bitmaps of one kind, so none of them
+// waits for another one of these).
+__device__ __forceinline__ void switch_bits(const HeapView &h, bool todo, uint32_t bmid, uint32_t pos, int dir)
+{
+    uint32_t lvl = 0;
+    for (uint32_t it = 0;; ++it) {
+        if (todo) {
+            uint64_t *const w = h.bm_word(bmid, lvl, pos >> 6);
+            const uint64_t bit = 1ull << (pos & 63);
+            const uint64_t prev = dir > 0 ? aor(w, bit) : aand(w, ~bit);
+            const bool was = (prev & bit) != 0;
+            if (was != (dir > 0)) {
+                todo = !(dir > 0 ? prev != 0 : prev != bit) && lvl + 1 < h.nlev;
+                ++lvl;
+                pos >>= 6;
+            }
+        }
+        const uint64_t pending = __ballot(todo);
+        if (pending == 0) return;
+        if (lane_id() == (uint32_t)(__ffsll((unsigned long long)pending) - 1)) count_event(h, EV_SPIN);
+        if (it >= h.spin_limit) {
+            if (todo) raise_error(h, ERR_SPIN);
+            return;
+        }
+    }
+}
+
+// ... for a block a lane, the lanes' blocks distinct (mask 0 = none), side by
+// side.  Returns whether the lane's slots were live; the caller counts the
+// deletions.  Converged call.  A step for all lanes after the other, not a
+// queue of switches a lane: 28 vector registers less.
+__device__ __forceinline__ bool release_beside(const HeapView &h, uint32_t cls, uint32_t bid, uint64_t mask)
+{
+    uint64_t *const p = h.alloc_bm + bid;
+    const uint64_t prev = mask ? aand(p, ~mask) : 0;
+    const bool ok = mask && (prev & mask) == mask;
+    if (mask && !ok) raise_error(h, ERR_BADHANDLE);
+    switch_bits(h, ok && prev == ~0ull, bm_active(cls), bid, +1);
+    bool empty = ok && (prev & ~mask) == 0;
+    for (int attempt = 0; attempt < kInvalidateAttempts && __ballot(empty); ++attempt) {
+        bool freed = false, owed = false;
+        uint32_t t = 0;
+        if (empty) {
+            const uint64_t before = aor(p, ~0ull);
+            empty = before != ~0ull;
+            if (empty) {
+                t = ald32(h.type + bid);
+                if (before == 0) {
+                    __hip_atomic_store(h.type + bid, kNull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    freed = true;
+                } else {
+                    const uint64_t before_rb = aand(p, before);
+                    owed = before_rb != ~0ull;
+                    empty = (before_rb & before) == 0;
+                }
+            }
+        }
+        complete_prior();
+        switch_bits(h, freed || owed, bm_active(t), bid, -1);
+        switch_bits(h, freed, bm_alloc(t), bid, -1);
+        switch_bits(h, freed, BM_FREE, bid, +1);
+        empty = empty && !freed;
+    }
+    return ok;
 }
 
 // The leader's part of Alg. allocate with request coalescing: find an active
@@ -688,7 +710,7 @@ __device__ __forceinline__ uint64_t wave_or64(uint64_t v)
 // share a block are released together, one atomic per distinct block (the
 // multi-slot release of sec.5.3.2), and all the wavefront's blocks side by
 // side: the first lane of each group holds the group's slots and makes its
-// release, and their bitmap switches complete in one converged loop.
+// release.
 // A release is a chain of dependent atomics (the block's bitmap, then a
 // switch per level it passes on to), 1-2 us however many lanes make it: one
 // block after the other, as handles in no order name them, took 7 times as
@@ -721,17 +743,11 @@ __device__ __forceinline__ void wave_release_handles(const HeapView &h, uint32_t
             if (n != (uint32_t)__popcll(group)) raise_error(h, ERR_BADHANDLE);
         }
     }
-    OpQueue q;
-    q.reset();
-    bool failed = false;
-    if (mine) {
-        const uint32_t cls = cls_of(handle >> 6);
-        failed = cls == kNull || !release_slots_uncounted(h, cls, handle >> 6, mine, q);
-    }
+    const uint32_t cls = mine ? cls_of(handle >> 6) : kNull;
+    const bool failed = !release_beside(h, cls, handle >> 6, cls == kNull ? 0 : mine) && mine;
     for (uint64_t f = __ballot(failed); f; f &= f - 1)
         count -= (uint32_t)__builtin_amdgcn_readlane(__popcll(mine), (uint32_t)(__ffsll((unsigned long long)f) - 1));
     if (lane == first && count) count_events(h, EV_DELS, count);
-    run_ops_wave(h, q);
 }
 
 // Deallocation of arbitrary handles of class `cls` (one per lane with want).
