@@ -22,6 +22,7 @@ struct GenK {
     int32_t dying;
     uint32_t c_state, c_count, c_id;   // Cell fields
     uint32_t a_id, a_left, a_new;      // Alive fields
+    RowOf row_of;                      // of W
 };
 
 // a Cell handle from the caller's grid array names a block of the heap
@@ -33,8 +34,8 @@ __device__ __forceinline__ bool gen_valid(const HeapView &h, uint32_t handle)
 }
 
 // Cell::count - live neighbours on the torus (dying cells do not count).
-// One integer division per cell, neighbour wrap-around by compare and select,
-// two blocks per wavefront iteration (as the Game of Life's count).
+// Neighbour wrap-around by compare and select, two blocks per wavefront
+// iteration (as the Game of Life's count).
 template <int U>
 __global__ __launch_bounds__(1024) void k_gen_count(HeapView h, GenK p)
 {
@@ -52,10 +53,21 @@ __global__ __launch_bounds__(1024) void k_gen_count(HeapView h, GenK p)
                 live[j] = false;
             }
         }
+        bool runs = true;
+#pragma unroll
+        for (int j = 0; j < U; ++j) runs = runs && row_run(__ballot(live[j]), id[j], p.W, p.row_of);
+        if (runs) {
+            int32_t n[U];
+            count_row_runs<U>(h, p.cells, p.W, p.H, p.row_of, p.c_state, id, bad, n,
+                              [](uint8_t st) { return (int32_t)(st == 1); });
+#pragma unroll
+            for (int j = 0; j < U; ++j) farr<int32_t>(h, bid[j], p.c_count)[s] = n[j];
+            return;
+        }
         uint32_t hc[U][8];
 #pragma unroll
         for (int j = 0; j < U; ++j) {
-            const int32_t y = id[j] / p.W, x = id[j] - y * p.W;
+            const int32_t y = p.row_of(id[j]), x = id[j] - y * p.W;
             const int32_t xs[3] = {x == 0 ? p.W - 1 : x - 1, x, x == p.W - 1 ? 0 : x + 1};
             const int32_t rows[3] = {(y == 0 ? p.H - 1 : y - 1) * p.W, y * p.W,
                                      (y == p.H - 1 ? 0 : y + 1) * p.W};
@@ -158,6 +170,7 @@ smmo_status bind_generation(smmo_heap *h, const smmo_generation_args &a, GenK &k
     k.cells = a.cells;
     k.W = a.width;
     k.H = a.height;
+    k.row_of = row_of_width(a.width);
     k.survive = a.survive;
     k.birth = a.birth;
     k.dying = a.dying;

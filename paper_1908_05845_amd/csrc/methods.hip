@@ -34,6 +34,7 @@ struct GolK {
     uint32_t wpg;                      // wavefronts per work-group of this launch
     uint32_t snap;                     // Cell::count: also take the Alive snapshot of every block
     uint32_t death_groups;             // fused generation: work-groups that run Alive::death
+    RowOf row_of;                      // of W
 };
 
 // a Cell handle from the caller's grid array names a block of the heap
@@ -44,8 +45,7 @@ __device__ __forceinline__ bool gol_valid(const HeapView &h, uint32_t handle)
     return false;
 }
 
-// Cell::count - live cells among the 8 neighbours on the torus.  One
-// integer division per cell (gfx950 has no integer divide instruction); the
+// Cell::count - live cells among the 8 neighbours on the torus; the
 // wrap-around of the neighbour coordinates is a compare and select.  U
 // blocks at once: a wavefront issues the neighbour-handle loads and then the
 // state loads of all U blocks before it waits, since each block's chain of
@@ -80,10 +80,21 @@ __global__ __launch_bounds__(1024) void k_gol_count(HeapView h, GolK p)
                 live[j] = false;
             }
         }
+        bool runs = true;
+#pragma unroll
+        for (int j = 0; j < U; ++j) runs = runs && row_run(__ballot(live[j]), id[j], p.W, p.row_of);
+        if (runs) {
+            int32_t n[U];
+            count_row_runs<U>(h, p.cells, p.W, p.H, p.row_of, p.c_state, id, bad, n,
+                              [](uint8_t st) { return (int32_t)st; });
+#pragma unroll
+            for (int j = 0; j < U; ++j) farr<int32_t>(h, bid[j], p.c_count)[s] = n[j];
+            return;
+        }
         uint32_t hc[U][8];
 #pragma unroll
         for (int j = 0; j < U; ++j) {
-            const int32_t y = id[j] / p.W, x = id[j] - y * p.W;
+            const int32_t y = p.row_of(id[j]), x = id[j] - y * p.W;
             const int32_t xs[3] = {x == 0 ? p.W - 1 : x - 1, x, x == p.W - 1 ? 0 : x + 1};
             const int32_t rows[3] = {(y == 0 ? p.H - 1 : y - 1) * p.W, y * p.W,
                                      (y == p.H - 1 ? 0 : y + 1) * p.W};
@@ -229,6 +240,7 @@ smmo_status bind_gol(smmo_heap *h, const smmo_gol_args &a, GolK &k)
     k.cells = a.cells;
     k.W = a.width;
     k.H = a.height;
+    k.row_of = row_of_width(a.width);
     BIND(a.cell_class, "state", SMMO_U8, 1, &k.c_state, nullptr);
     BIND(a.cell_class, "count", SMMO_I32, 1, &k.c_count, nullptr);
     BIND(a.cell_class, "cell_id", SMMO_I32, 1, &k.c_id, nullptr);
@@ -236,8 +248,16 @@ smmo_status bind_gol(smmo_heap *h, const smmo_gol_args &a, GolK &k)
     return SMMO_OK;
 }
 
-// blocks per wavefront iteration of Cell::count unless set otherwise
-constexpr uint32_t kGolCountGroup = 2;
+// Blocks per wavefront iteration and work-group size of Cell::count unless set
+// otherwise.  The walk waits for memory; four blocks at once hide more of it
+// where the wavefronts have several iterations each (4096 x 4096 cells, warm:
+// 71 us against 83 with two; 2048 x 2048 21.8 and 23.8), two where they have
+// one or two (1024 x 1024: 8.7 us against 9.3 with four).
+constexpr uint32_t kGolCountFew = 65536;      // 2048 x 2048 cells
+LaunchShape gol_count_shape(const smmo_heap *h, uint32_t cls)
+{
+    return h->ub_blocks[cls] < kGolCountFew ? method_shape(h, cls, 2) : method_shape(h, cls, 4, 128);
+}
 
 template <int Which>
 smmo_status launch_gol(smmo_heap *h, uint32_t cls, const void *args, hipStream_t st)
@@ -252,7 +272,7 @@ smmo_status launch_gol(smmo_heap *h, uint32_t cls, const void *args, hipStream_t
     k.death_groups = 0;
     const uint32_t want = Which == 1 ? a.alive_class : a.cell_class;
     if (cls != want) return fail(SMMO_EINVAL, "gol: method runs on a different class");
-    const LaunchShape ls = method_shape(h, cls, Which == 0 ? kGolCountGroup : 0);
+    const LaunchShape ls = Which == 0 ? gol_count_shape(h, cls) : method_shape(h, cls, 0);
     k.wpg = ls.block.x / 64;
     if ((s = ensure_enumerated(h, cls, false, st, Which == 1 && packing_wanted(h, cls, ls)))) return s;
     if (Which == 0) {
@@ -290,7 +310,7 @@ smmo_status run_gol_generation(smmo_heap *h, uint32_t cls, const void *args, hip
     if (cls != a.cell_class) return fail(SMMO_EINVAL, "gol: method runs on a different class");
     const bool direct = h->v.M <= kDirectMaxBlocks;
     if (!direct && (s = ensure_enumerated(h, a.alive_class, true, st, false, false))) return s;
-    const LaunchShape lc = method_shape(h, cls, kGolCountGroup);
+    const LaunchShape lc = gol_count_shape(h, cls);
     if ((s = ensure_enumerated(h, cls, false, st))) return s;
     k.wpg = lc.block.x / 64;
     k.snap = direct ? 1u : 0u;
