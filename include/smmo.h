@@ -43,9 +43,13 @@
  *     the methods' reads and writes of fields do not conflict.
  *   - Device pointers are addresses in device memory of the GPU the heap is
  *     on.  The caller owns every buffer it passes and keeps it alive until the
- *     work that uses it has completed.  libsmmo allocates no device memory:
- *     the heap and all of its internal arrays are carved out of the buffer
- *     given to smmo_alloc_heap().
+ *     work that uses it has completed.  The heap and all of its internal
+ *     arrays are carved out of the buffer given to smmo_alloc_heap().  The one
+ *     thing that libsmmo allocates is a workspace of nbody.force's per class,
+ *     on its first call on 12 to 1,536 blocks (134 MB for 65,536 bodies; from
+ *     the heap's allocator callback if it has one, never under graph
+ *     capture), kept until smmo_heap_free(); where there is none to be had
+ *     the method takes a kernel that needs none.
  *   - Handles are 32-bit: (block index << 6) | slot.  SMMO_NULL names no
  *     object.  Handles of live objects are < 2^31, so the top bit is free for
  *     the caller to use as a flag in handle-valued fields.

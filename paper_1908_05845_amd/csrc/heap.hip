@@ -971,9 +971,16 @@ void *class_workspace(smmo_heap *h, uint32_t cls, size_t bytes, hipStream_t st)
     w->bytes = cur ? bytes + bytes / 2 : bytes;
     if (h->owner.alloc) {
         w->p = h->owner.alloc(w->bytes, h->owner.ctx);
-    } else if (hipMalloc(&w->p, w->bytes) != hipSuccess) {
-        (void)hipGetLastError();
-        w->p = nullptr;
+    } else {
+        // (another stream may be captured just now, which an allocation in the
+        // thread's default mode would break)
+        hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+        const bool swapped = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+        if (hipMalloc(&w->p, w->bytes) != hipSuccess) {
+            (void)hipGetLastError();
+            w->p = nullptr;
+        }
+        if (swapped) (void)hipThreadExchangeStreamCaptureMode(&mode);
     }
     if (!w->p) {
         delete w;
