@@ -140,7 +140,7 @@ __global__ void k_heap_init(HeapView h)
 
 // Enumeration pre-pass (sec.5.2.7 with Alg. indices of sec.5.3.1): compact
 // the set bits of allocated[cls] into R.  A wavefront takes kPer containers
-// of level 0, a work-group the 16 kPer of its wavefronts (every container is
+// of level 0 (a lane reads one), a work-group the 16 kPer of its wavefronts (every container is
 // read: the level-1 summary would only add a dependent load for 8 bytes per
 // 64 blocks).  A lane takes one block of a container, so bitmaps are read and
 // R is written in runs.  The packing plan (split): blocks with more than 32
@@ -163,12 +163,16 @@ __global__ void k_heap_init(HeapView h)
 // writing the entries of each, one CU wrote what 65,536 blocks list.  A full
 // list of 294,000 blocks 50 us, 7.6 now; wa-tor on 1024 x 1024 cells 9 and
 // 5.3.  With snapshot and plan, launch included, 65,536 full blocks 53 us and
-// 11, 1M 59 and 14, 4M 59 and 20, 16M 60 and 49; 4,096 15 and 10.5.
+// 11, 1M 59 and 14, 4M 59 and 20, 16M 60 and 42; 4,096 15 and 10.5.  Empty
+// containers are passed over by a ballot: 1,024 full blocks in a heap of 2^24
+// 12.0 us and 9.5.
 constexpr uint64_t kPackMask = (1ull << 25) - 1;
 constexpr uint32_t kFewContainers = 1024;     // in order: one container a thread
-constexpr uint32_t kManyContainers = 16384;   // beyond: 16 containers a wavefront, for the atomics' sake
+// beyond: 16 and 64 containers a wavefront, for the atomics' sake
+constexpr uint32_t kManyContainers = 16384, kMostContainers = 65536;
 static_assert(kMaxBlocks <= kPackMask, "block counts must fit the packed enumeration counter");
-static_assert((kMaxBlocks / 64 + 256) / 256 < (1u << 14) && kManyContainers / 64 < (1u << 14),
+static_assert((kMaxBlocks / 64 + 1024) / 1024 < (1u << 14) && kMostContainers / 256 < (1u << 14) &&
+                  kManyContainers / 64 < (1u << 14),
               "work-group counts must fit the packed enumeration counter");
 
 template <int kPer>
@@ -177,40 +181,49 @@ __global__ __launch_bounds__(1024) void k_enumerate(HeapView h, uint32_t cls, ui
 {
     constexpr int kBatch = kPer < 8 ? kPer : 8;
     constexpr uint32_t kGroup = 16 * kPer;
-    __shared__ uint64_t s_c[kGroup], s_d[kGroup];
     __shared__ uint64_t s_all[kFewContainers];
     __shared__ uint32_t s_nd[16], s_ns[16], s_bd[16], s_bs[16];
     __shared__ uint32_t s_kd, s_ks;
     const uint32_t lane = lane_id(), wig = threadIdx.x >> 6;
     const uint32_t n0 = h.lvl_n[0];
     const uint32_t base = blockIdx.x * kGroup;
+    const uint32_t first = base + wig * kPer;            // the wavefront's first container
     const uint64_t *const C = h.bm_word(bm_alloc(cls), 0, 0);
     const bool ok = ald32(h.ctrl + CTRL_ERR) == 0;       // a failed heap lists nothing
     // No wavefront changes a bitmap while this kernel runs, so plain loads
     // are enough.
     const uint64_t mine = ok && ordered && threadIdx.x < n0 ? C[threadIdx.x] : 0ull;
-
-    uint32_t nd = 0, ns = 0;
-    for (int u0 = 0; u0 < kPer; u0 += kBatch) {
-        const uint32_t j0 = wig * kPer + u0;
-        uint64_t c[kBatch], bm[kBatch];
+    // lane j: container first + j and its dense blocks
+    const uint64_t cl = ok && lane < kPer && first + lane < n0 ? C[first + lane] : 0ull;
+    const uint64_t some = __ballot(cl != 0);
+    uint64_t dl = cl;
+    if (snapshot | split) {
+        for (uint64_t g = some; g;) {
+            uint32_t j[kBatch];
+            uint64_t c[kBatch], bm[kBatch];
 #pragma unroll
-        for (int u = 0; u < kBatch; ++u) c[u] = ok && base + j0 + u < n0 ? uniform64(C[base + j0 + u]) : 0ull;
+            for (int u = 0; u < kBatch; ++u) {
+                j[u] = g ? (uint32_t)(__ffsll((unsigned long long)g) - 1) : 0u;
+                c[u] = g ? lane64(cl, j[u]) : 0ull;
+                g &= g - 1;
+            }
 #pragma unroll
-        for (int u = 0; u < kBatch; ++u)
-            bm[u] = (snapshot | split) && ((c[u] >> lane) & 1) ? h.alloc_bm[(uint64_t)(base + j0 + u) * 64 + lane] : 0ull;
+            for (int u = 0; u < kBatch; ++u)
+                bm[u] = (c[u] >> lane) & 1 ? h.alloc_bm[(uint64_t)(first + j[u]) * 64 + lane] : 0ull;
 #pragma unroll
-        for (int u = 0; u < kBatch; ++u) {
-            const bool in = (c[u] >> lane) & 1;
-            if (snapshot && in) h.iter_bm[(uint64_t)(base + j0 + u) * 64 + lane] = bm[u];
-            const uint64_t d = split ? __ballot(in && __popcll(bm[u]) > 32) : c[u];
-            nd += (uint32_t)__popcll(d);
-            ns += (uint32_t)__popcll(c[u] & ~d);
-            if (lane == 0) {
-                s_c[j0 + u] = c[u];
-                s_d[j0 + u] = d;
+            for (int u = 0; u < kBatch; ++u) {
+                const bool in = (c[u] >> lane) & 1;
+                if (snapshot && in) h.iter_bm[(uint64_t)(first + j[u]) * 64 + lane] = bm[u];
+                const uint64_t d = __ballot(in && __popcll(bm[u]) > 32);
+                if (split && c[u] && lane == j[u]) dl = d;
             }
         }
+    }
+    uint32_t nd = (uint32_t)__popcll(dl), ns = (uint32_t)__popcll(cl & ~dl);
+#pragma unroll
+    for (int d = 1; d < kPer; d <<= 1) {
+        nd += (uint32_t)__shfl_xor((int)nd, d);
+        ns += (uint32_t)__shfl_xor((int)ns, d);
     }
     uint32_t bd = 0, bs = 0;                             // of the work-groups before this one
     if (ordered) {
@@ -281,10 +294,9 @@ __global__ __launch_bounds__(1024) void k_enumerate(HeapView h, uint32_t cls, ui
     }
     uint32_t *R = h.R + (uint64_t)cls * h.M;
     const uint64_t below = (1ull << lane) - 1;
-#pragma unroll 4
-    for (uint32_t j = wig * kPer; j < (wig + 1) * kPer; ++j) {
-        const uint64_t c = uniform64(s_c[j]), d = uniform64(s_d[j]), sp = c & ~d;
-        const uint32_t b = (base + j) * 64 + lane;
+    for (uint64_t g = some; g; g &= g - 1) {
+        const uint32_t j = (uint32_t)(__ffsll((unsigned long long)g) - 1), b = (first + j) * 64 + lane;
+        const uint64_t c = lane64(cl, j), d = lane64(dl, j), sp = c & ~d;
         if ((d >> lane) & 1) R[kd + (uint32_t)__popcll(d & below)] = b;
         else if ((sp >> lane) & 1) R[h.M - 1 - (ks + (uint32_t)__popcll(sp & below))] = b;
         kd += (uint32_t)__popcll(d);
@@ -920,9 +932,10 @@ smmo_status ensure_enumerated(smmo_heap *h, uint32_t cls, bool snapshot, hipStre
     // can use it, a packed one of its own visits objects in no order.
     const uint32_t n0 = h->v.lvl_n[0];
     const uint32_t ordered = n0 <= kFewContainers && (!split || in_order) ? 1u : 0u;
-    const dim3 grid(n0 <= kManyContainers ? (n0 + 63) / 64 : (n0 + 255) / 256);
-    hipLaunchKernelGGL(n0 <= kManyContainers ? k_enumerate<4> : k_enumerate<16>, grid, dim3(1024), 0, st, h->v, cls,
-                       snapshot ? 1u : 0u, split ? 1u : 0u, ordered);
+    const uint32_t per = n0 <= kManyContainers ? 4 : n0 <= kMostContainers ? 16 : 64;
+    hipLaunchKernelGGL(per == 4 ? k_enumerate<4> : per == 16 ? k_enumerate<16> : k_enumerate<64>,
+                       dim3((n0 + 16 * per - 1) / (16 * per)), dim3(1024), 0, st, h->v, cls, snapshot ? 1u : 0u,
+                       split ? 1u : 0u, ordered);
     smmo_status s = launch_check("k_enumerate");
     if (s) return s;
     state = split ? R_SPLIT : R_VALID;
