@@ -506,18 +506,23 @@ __global__ __launch_bounds__(256) void k_destroy(HeapView h, uint32_t cls, const
 }
 
 // Second launch: brings the states of the class's blocks in line with their
-// slots, 64 blocks of one container a wavefront.  A block without objects
+// slots, a container's 64 blocks at a time, `per` containers a wavefront (a
+// lane reads one, those without blocks of the class are passed over).  A block without objects
 // becomes free (its type unset, its slots all taken, as a release
 // leaves it), one with free slots active.  Nothing else runs on the heap, so
 // a container is its wavefront's own; what passes on to the next levels goes
 // through the switches that other wavefronts' containers meet there.
-__global__ __launch_bounds__(256) void k_destroy_settle(HeapView h, uint32_t cls)
+__global__ __launch_bounds__(256) void k_destroy_settle(HeapView h, uint32_t cls, uint32_t per)
 {
     const uint32_t lane = lane_id(), waves = gridDim.x * (blockDim.x >> 6);
-    for (uint32_t c = global_wave_id(); c < h.lvl_n[0]; c += waves) {
+    const uint32_t c0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)global_wave_id());
+    // (every waves-th container: a class's blocks lie together)
+    const uint64_t at = (uint64_t)lane * waves + c0;
+    const uint64_t owned = lane < per && at < h.lvl_n[0] ? *h.bm_word(bm_alloc(cls), 0, (uint32_t)at) : 0ull;
+    for (uint64_t g = __ballot(owned != 0); g; g &= g - 1) {
+        const uint32_t j = (uint32_t)(__ffsll((unsigned long long)g) - 1), c = j * waves + c0;
         uint64_t *const alloc = h.bm_word(bm_alloc(cls), 0, c), *const active = h.bm_word(bm_active(cls), 0, c);
-        const uint64_t mine = uniform64(*alloc);
-        if (!mine) continue;
+        const uint64_t mine = lane64(owned, j);
         const uint64_t was = uniform64(*active);
         const uint32_t bid = c * 64 + lane;
         const uint64_t slots = (mine >> lane) & 1 ? h.alloc_bm[bid] : ~0ull;
@@ -1438,8 +1443,11 @@ smmo_status smmo_destroy(smmo_heap *h, uint32_t class_id, const uint32_t *handle
     const uint32_t grid = (uint32_t)(((uint64_t)n + 255) / 256);
     hipLaunchKernelGGL(k_destroy, dim3(grid), dim3(256), 0, st, h->v, class_id, handles, n);
     if ((s = launch_check("k_destroy"))) return s;
-    const uint32_t sgrid = std::min((h->v.lvl_n[0] + 3) / 4, 2048u);
-    hipLaunchKernelGGL(k_destroy_settle, dim3(sgrid), dim3(256), 0, st, h->v, class_id);
+    // a container a wavefront as long as 8,192 wavefronts do
+    const uint32_t per = (h->v.lvl_n[0] + 8191) / 8192;
+    static_assert((kMaxBlocks / 64 + 1 + 8191) / 8192 <= 64, "a wavefront's containers must fit its lanes");
+    hipLaunchKernelGGL(k_destroy_settle, dim3((h->v.lvl_n[0] + 4 * per - 1) / (4 * per)), dim3(256), 0, st, h->v,
+                       class_id, per);
     if ((s = launch_check("k_destroy_settle"))) return s;
     h->last = st;
     return SMMO_OK;
