@@ -181,7 +181,7 @@ constexpr int kMaxOps = 6;
 
 // Invalidation attempts of one block (Alg. invalidate with rollback) before
 // the release that emptied it gives up, and the most switches one release
-// queues: a re-activation, a rollback per failed attempt but the last, and
+// makes, which a queue holds: a re-activation, a rollback per failed attempt but the last, and
 // the three switches of a successful invalidation.
 constexpr int kInvalidateAttempts = kMaxOps - 3;
 constexpr int kMaxReleaseOps = 1 + (kInvalidateAttempts - 1) + 3;
