@@ -7,6 +7,8 @@ smmo_gather_soa (ordered by the objects' key fields, since slot placement is
 not part of the result).  Everything runs through libsmmo.
 """
 
+import operator
+
 import numpy as np
 
 from . import smmo
@@ -61,6 +63,11 @@ def _blocks(n: int) -> int:
 
 def _np(t):
     return t.detach().cpu().numpy()
+
+
+def _count(n):
+    """A number of steps as range() takes it: whole, none below zero."""
+    return max(operator.index(n), 0)
 
 
 def _repeat(heap, args, launches, n, stream):
@@ -414,7 +421,7 @@ class SpringSim:
 
     def step(self, n: int = 1, stream=None):
         a = self.args
-        steps = smmo.smmo_spring_steps_args(a.node_class, a.spring_class, a.dt, a.strain_limit, a.flags, n)
+        steps = smmo.smmo_spring_steps_args(a.node_class, a.spring_class, a.dt, a.strain_limit, a.flags, _count(n))
         smmo.smmo_parallel_do(self.heap.h, self.heap.cls["Spring"], self.m_steps, steps, stream)
 
     def read(self):
