@@ -51,13 +51,21 @@ typedef struct {
  * Body {pos_x, pos_y, vel_x, vel_y, force_x, force_y, mass: F32}
  * "nbody.force"  : force = sum over all other bodies j (a device_do over the
  *                  class) of G m m_j (x_j - x) / (|x_j - x|^2 + eps^2)^(3/2)
- * "nbody.update" : vel += force / mass * dt; pos += vel * dt               */
+ * "nbody.update" : vel += force / mass * dt; pos += vel * dt
+ * "nbody.steps"  : `steps` times "nbody.force", then "nbody.update"        */
 typedef struct {
     float G;
     float eps;
     float dt;
     uint32_t reserved;
 } smmo_nbody_args;
+
+typedef struct {                /* smmo_nbody_args, and */
+    float G;
+    float eps;
+    float dt;
+    uint32_t steps;
+} smmo_nbody_steps_args;
 
 /* ---- spring-mass mesh (thesis Ch.7 "structure", compute steps) -----------
  * Node   {x, y, vx, vy, m: F32, adj: HANDLE x 8}

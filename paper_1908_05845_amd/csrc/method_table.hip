@@ -23,6 +23,7 @@ smmo_status launch_ls_free(smmo_heap *h, uint32_t cls, const void *args, hipStre
 // launchers defined in nbody.hip
 smmo_status launch_nbody_force(smmo_heap *h, uint32_t cls, const void *args, hipStream_t st);
 smmo_status launch_nbody_update(smmo_heap *h, uint32_t cls, const void *args, hipStream_t st);
+smmo_status launch_nbody_steps(smmo_heap *h, uint32_t cls, const void *args, hipStream_t st);
 
 // launchers defined in spring.hip
 smmo_status launch_spring_force(smmo_heap *h, uint32_t cls, const void *args, hipStream_t st);
@@ -122,6 +123,7 @@ const MethodEntry kMethods[] = {
     {"spring.steps", sizeof(smmo_spring_steps_args), launch_spring_steps},
     {"adjoint.step", sizeof(smmo_adjoint_pass_args), launch_adj_pass_step},
     {"adjoint.reverse", sizeof(smmo_adjoint_pass_args), launch_adj_pass_reverse},
+    {"nbody.steps", sizeof(smmo_nbody_steps_args), launch_nbody_steps},
 };
 } // namespace
 

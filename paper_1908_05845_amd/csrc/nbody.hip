@@ -277,11 +277,26 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(4, 4))) 
     reinterpret_cast<float *>(pl.part)[2 * ((uint64_t)slot * pl.stride + i) + ((lane >> 4) & 1)] = v[0];
 }
 
+// v += f / m dt; x += v dt (velocity first)
+__device__ __forceinline__ void nbody_move(float dt, float fx, float fy, float m, float &vx, float &vy, float &x,
+                                           float &y)
+{
+    vx += fx / m * dt;
+    vy += fy / m * dt;
+    x += vx * dt;
+    y += vy * dt;
+}
+
 // Adds up each body's partial sums with Kahan compensation and stores its
 // force: a work-group per listed block, whose four wavefronts take a quarter
 // of the slots each, in order, eight rows in flight (one wavefront a block
 // took 25 us over the 128 rows of 65,536 bodies: too few loads in flight).
-template <int W>
+// kMove: also Body::update of the body, which no other work-group of the
+// launch reads.  A step of a few thousand bodies is three launches near the
+// launch floor (3,001 bodies: 9.0, 3.3 and 3.3 us and the gaps between them);
+// this one saves the third: eight steps and their read-back 273 us with it and
+// 247 without.
+template <int W, bool kMove>
 __global__ __launch_bounds__(256) void k_nbody_sum(HeapView h, NbodyK p, PairPlan pl)
 {
     __shared__ float2 red[4][64];
@@ -296,6 +311,13 @@ __global__ __launch_bounds__(256) void k_nbody_sum(HeapView h, NbodyK p, PairPla
     const uint32_t t = h.type[bid];
     const uint64_t bm = h.alloc_bm[bid];
     const float m = farr<float>(h, bid, p.o_m)[s];
+    float vx = 0.f, vy = 0.f, x = 0.f, y = 0.f;
+    if (kMove && w == 0) {
+        vx = farr<float>(h, bid, p.o_vx)[s];
+        vy = farr<float>(h, bid, p.o_vy)[s];
+        x = farr<float>(h, bid, p.o_x)[s];
+        y = farr<float>(h, bid, p.o_y)[s];
+    }
     float ax = 0.f, ay = 0.f, cx = 0.f, cy = 0.f;
     for (uint32_t k = lo; k < hi; k += 8) {
         float2 v[8];
@@ -320,12 +342,18 @@ __global__ __launch_bounds__(256) void k_nbody_sum(HeapView h, NbodyK p, PairPla
         ax += red[k][s].x;
         ay += red[k][s].y;
     }
-    const float gm = p.G * m;
-    farr<float>(h, bid, p.o_fx)[s] = gm * ax;
-    farr<float>(h, bid, p.o_fy)[s] = gm * ay;
+    const float gm = p.G * m, fx = gm * ax, fy = gm * ay;
+    farr<float>(h, bid, p.o_fx)[s] = fx;
+    farr<float>(h, bid, p.o_fy)[s] = fy;
+    if (!kMove) return;
+    nbody_move(p.dt, fx, fy, m, vx, vy, x, y);
+    farr<float>(h, bid, p.o_vx)[s] = vx;
+    farr<float>(h, bid, p.o_vy)[s] = vy;
+    farr<float>(h, bid, p.o_x)[s] = x;
+    farr<float>(h, bid, p.o_y)[s] = y;
 }
 
-// Body::update - v += f / m dt; x += v dt (velocity first)
+// Body::update
 __global__ __launch_bounds__(1024) void k_nbody_update(HeapView h, NbodyK p)
 {
     for_each_block(h, p.cls, false, [&](uint32_t bid, uint64_t bm) {
@@ -333,12 +361,12 @@ __global__ __launch_bounds__(1024) void k_nbody_update(HeapView h, NbodyK p)
         if (!((bm >> s) & 1)) return;
         const float m = farr<float>(h, bid, p.o_m)[s];
         float vx = farr<float>(h, bid, p.o_vx)[s], vy = farr<float>(h, bid, p.o_vy)[s];
-        vx += farr<float>(h, bid, p.o_fx)[s] / m * p.dt;
-        vy += farr<float>(h, bid, p.o_fy)[s] / m * p.dt;
+        float x = farr<float>(h, bid, p.o_x)[s], y = farr<float>(h, bid, p.o_y)[s];
+        nbody_move(p.dt, farr<float>(h, bid, p.o_fx)[s], farr<float>(h, bid, p.o_fy)[s], m, vx, vy, x, y);
         farr<float>(h, bid, p.o_vx)[s] = vx;
         farr<float>(h, bid, p.o_vy)[s] = vy;
-        farr<float>(h, bid, p.o_x)[s] += vx * p.dt;
-        farr<float>(h, bid, p.o_y)[s] += vy * p.dt;
+        farr<float>(h, bid, p.o_x)[s] = x;
+        farr<float>(h, bid, p.o_y)[s] = y;
     });
 }
 
@@ -394,13 +422,33 @@ uint64_t pair_rows(uint64_t slots, const PairShape &s)
 }
 
 template <int W>
-void launch_pairs(smmo_heap *h, const NbodyK &k, const PairPlan &pl, uint64_t blocks, hipStream_t st)
+void launch_pairs(smmo_heap *h, const NbodyK &k, const PairPlan &pl, uint64_t blocks, bool move, hipStream_t st)
 {
     const uint64_t segs = (64 * blocks + pl.J - 1) / pl.J;
     const dim3 grid((uint32_t)(pl.J / (32 * W) * (segs * (segs + 1) / 2)));
     if (k.eps2 > 0.f) hipLaunchKernelGGL((k_nbody_pairs<W, false>), grid, dim3(64 * W), 0, st, h->v, k, pl);
     else hipLaunchKernelGGL((k_nbody_pairs<W, true>), grid, dim3(64 * W), 0, st, h->v, k, pl);
-    hipLaunchKernelGGL(k_nbody_sum<W>, dim3((uint32_t)blocks), dim3(256), 0, st, h->v, k, pl);
+    if (move) hipLaunchKernelGGL((k_nbody_sum<W, true>), dim3((uint32_t)blocks), dim3(256), 0, st, h->v, k, pl);
+    else hipLaunchKernelGGL((k_nbody_sum<W, false>), dim3((uint32_t)blocks), dim3(256), 0, st, h->v, k, pl);
+}
+
+// The pair kernel's plan for class cls, whose list is ready: whether it takes
+// the pair form, and then the workspace that holds the partial sums.
+bool pair_plan(smmo_heap *h, uint32_t cls, uint64_t blocks, PairShape &sh, PairPlan &pl, hipStream_t st)
+{
+    sh = pair_shape(blocks);
+    if (!sh.W || h->replayed[cls] || ((h->v.direct >> cls) & 1)) return false;
+    const uint64_t I = 32 * sh.W, stride = (64 * blocks + I - 1) / I * I;
+    float2 *part = static_cast<float2 *>(class_workspace(h, cls, pair_rows(64 * blocks, sh) * stride * sizeof(float2), st));
+    pl = PairPlan{part, (uint32_t)stride, sh.J};
+    return part != nullptr;
+}
+
+void run_pairs(smmo_heap *h, const NbodyK &k, const PairShape &sh, const PairPlan &pl, uint64_t blocks, bool move,
+               hipStream_t st)
+{
+    if (sh.W == 4) launch_pairs<4>(h, k, pl, blocks, move, st);
+    else launch_pairs<8>(h, k, pl, blocks, move, st);
 }
 
 smmo_status nbody_force_launch(smmo_heap *h, uint32_t cls, const void *args, hipStream_t st)
@@ -413,16 +461,11 @@ smmo_status nbody_force_launch(smmo_heap *h, uint32_t cls, const void *args, hip
     if (s) return s;
     if ((s = ensure_enumerated(h, cls, false, st))) return s;
     const uint64_t blocks = std::max<uint64_t>(1, h->ub_blocks[cls]);
-    const PairShape sh = pair_shape(blocks);
-    if (sh.W && !h->replayed[cls] && !((h->v.direct >> cls) & 1)) {
-        const uint64_t I = 32 * sh.W, stride = (64 * blocks + I - 1) / I * I;
-        float2 *part = static_cast<float2 *>(class_workspace(h, cls, pair_rows(64 * blocks, sh) * stride * sizeof(float2), st));
-        if (part) {
-            const PairPlan pl{part, (uint32_t)stride, sh.J};
-            if (sh.W == 4) launch_pairs<4>(h, k, pl, blocks, st);
-            else launch_pairs<8>(h, k, pl, blocks, st);
-            return launched("k_nbody_pairs");
-        }
+    PairShape sh;
+    PairPlan pl;
+    if (pair_plan(h, cls, blocks, sh, pl, st)) {
+        run_pairs(h, k, sh, pl, blocks, false, st);
+        return launched("k_nbody_pairs");
     }
     const uint32_t grid = (uint32_t)std::min<uint64_t>(blocks, 8192);
     if (k.eps2 > 0.f)
@@ -445,9 +488,48 @@ smmo_status nbody_update_launch(smmo_heap *h, uint32_t cls, const void *args, hi
     return launched("k_nbody_update");
 }
 
+// nbody.steps on Body: `steps` times nbody.force and nbody.update, a body moved
+// by the launch that adds up its force where the class takes the pair form and
+// no snapshot taken ahead waits for one of the two do-alls.
+smmo_status nbody_steps_launch(smmo_heap *h, uint32_t cls, const void *args, hipStream_t st)
+{
+    smmo_nbody_steps_args sa;
+    memcpy(&sa, args, sizeof sa);
+    const smmo_nbody_args a{sa.G, sa.eps, sa.dt, 0};
+    NbodyK k;
+    smmo_status s = cached_bind(h, (const void *)&nbody_steps_launch, cls, a, k,
+                                [&] { return bind_nbody(h, cls, a, k); });
+    if (s) return s;
+    if (sa.steps == 0) return SMMO_OK;
+    const uint64_t blocks = std::max<uint64_t>(1, h->ub_blocks[cls]);
+    PairShape sh;
+    PairPlan pl;
+    if (!((h->v.snap >> cls) & 1)) {
+        if ((s = ensure_enumerated(h, cls, false, st))) return s;
+        if (pair_plan(h, cls, blocks, sh, pl, st)) {
+            for (uint32_t t = 0; t < sa.steps; ++t) run_pairs(h, k, sh, pl, blocks, true, st);
+            return launched("k_nbody_pairs");
+        }
+    }
+    // as the two do-alls, with their launch shapes; a snapshot is the first one's
+    uint32_t force = 0, update = 0;
+    if ((s = smmo_method_id("nbody.force", &force)) || (s = smmo_method_id("nbody.update", &update))) return s;
+    const uint32_t method = h->cur_method;
+    for (uint32_t t = 0; t < sa.steps && !s; ++t) {
+        h->cur_method = force;
+        s = nbody_force_launch(h, cls, &a, st);
+        h->v.snap &= ~(1u << cls);
+        h->cur_method = update;
+        if (!s) s = nbody_update_launch(h, cls, &a, st);
+    }
+    h->cur_method = method;
+    return s;
+}
+
 } // namespace
 
 namespace smmo {
 smmo_status launch_nbody_force(smmo_heap *h, uint32_t c, const void *a, hipStream_t s) { return nbody_force_launch(h, c, a, s); }
 smmo_status launch_nbody_update(smmo_heap *h, uint32_t c, const void *a, hipStream_t s) { return nbody_update_launch(h, c, a, s); }
+smmo_status launch_nbody_steps(smmo_heap *h, uint32_t c, const void *a, hipStream_t s) { return nbody_steps_launch(h, c, a, s); }
 } // namespace smmo

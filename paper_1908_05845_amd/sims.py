@@ -333,6 +333,7 @@ class NbodySim:
         self.args = smmo.smmo_nbody_args(G, eps, dt, 0)
         self.m_force = smmo.smmo_method_id("nbody.force")
         self.m_update = smmo.smmo_method_id("nbody.update")
+        self.m_steps = smmo.smmo_method_id("nbody.steps")
         self.cls = self.heap.cls["Body"]
 
     def force(self, stream=None):
@@ -342,7 +343,9 @@ class NbodySim:
         smmo.smmo_parallel_do(self.heap.h, self.cls, self.m_update, self.args, stream)
 
     def step(self, n: int = 1, stream=None):
-        _repeat(self.heap.h, self.args, [(self.cls, self.m_force), (self.cls, self.m_update)], n, stream)
+        a = self.args
+        steps = smmo.smmo_nbody_steps_args(a.G, a.eps, a.dt, _count(n))
+        smmo.smmo_parallel_do(self.heap.h, self.cls, self.m_steps, steps, stream)
 
     def read(self):
         g = self.heap.gather("Body")

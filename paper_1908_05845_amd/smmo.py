@@ -78,6 +78,10 @@ class smmo_nbody_args(C.Structure):
     _fields_ = [("G", C.c_float), ("eps", C.c_float), ("dt", C.c_float), ("reserved", C.c_uint32)]
 
 
+class smmo_nbody_steps_args(C.Structure):
+    _fields_ = smmo_nbody_args._fields_[:3] + [("steps", C.c_uint32)]
+
+
 SMMO_SPRING_TENSION_ONLY = 1
 
 
