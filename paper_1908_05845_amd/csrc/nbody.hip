@@ -27,19 +27,17 @@ struct NbodyK {
 
 // Body::compute_force with device_do over all bodies (Ch.7 "nbody").  A
 // work-group owns one block of 64 bodies i (one per lane in every wave);
-// its four wavefronts split the other bodies j block-wise (wave w takes
-// every fourth block of R), stage each j-block in LDS and read it back as
-// broadcasts.  Each wave sums one j-block (64 terms) into a fresh float32
-// partial and adds the partial to its running sum with Kahan compensation;
-// the four running sums are combined in wave order.  The thesis leaves this
-// shared-memory tiling as future work (its "Further Optimizations").
-template <bool kGuard>
-__global__ __launch_bounds__(256) void k_nbody_force(HeapView h, NbodyK p)
+// its W wavefronts (four in k_nbody_force) split the other bodies j
+// block-wise (wave w takes every W-th block of R), stage each j-block in LDS
+// and read it back as broadcasts.  Each wave sums one j-block (64 terms) into
+// a fresh float32 partial and adds the partial to its running sum with Kahan
+// compensation; the W running sums are combined in wave order.  The thesis
+// leaves this shared-memory tiling as future work (its "Further
+// Optimizations").
+template <int W, bool kGuard>
+__device__ __forceinline__ void nbody_force_walk(const HeapView &h, const NbodyK &p, const BlockList &L,
+                                                 float4 (*tile)[64], float2 (*red)[64])
 {
-    __shared__ float4 tile[4][64];
-    __shared__ float2 red[4][64];
-    if (heap_failed(h)) return;
-    const BlockList L = block_list(h, p.cls);
     const uint32_t lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     for (uint32_t ib = xcd_logical_wg(); ib < L.r; ib += gridDim.x) {
         const uint32_t bid = L.at(ib);
@@ -48,7 +46,7 @@ __global__ __launch_bounds__(256) void k_nbody_force(HeapView h, NbodyK p)
         const float xi = farr<float>(h, bid, p.o_x)[lane];
         const float yi = farr<float>(h, bid, p.o_y)[lane];
         float ax = 0.f, ay = 0.f, cx = 0.f, cy = 0.f;
-        for (uint32_t j0 = 0; j0 < L.r; j0 += 4) {
+        for (uint32_t j0 = 0; j0 < L.r; j0 += W) {
             const uint32_t jt = j0 + w;
             if (jt >= L.r) break;                        // wave-uniform
             const uint32_t jb = __builtin_amdgcn_readfirstlane(L.at(jt));
@@ -89,7 +87,7 @@ __global__ __launch_bounds__(256) void k_nbody_force(HeapView h, NbodyK p)
         if (w == 0 && ((bmi >> lane) & 1)) {
             float sx = 0.f, sy = 0.f;
 #pragma unroll
-            for (int k = 0; k < 4; ++k) {
+            for (int k = 0; k < W; ++k) {
                 sx += red[k][lane].x;
                 sy += red[k][lane].y;
             }
@@ -99,6 +97,15 @@ __global__ __launch_bounds__(256) void k_nbody_force(HeapView h, NbodyK p)
         }
         __syncthreads();
     }
+}
+
+template <bool kGuard>
+__global__ __launch_bounds__(256) void k_nbody_force(HeapView h, NbodyK p)
+{
+    __shared__ float4 tile[4][64];
+    __shared__ float2 red[4][64];
+    if (heap_failed(h)) return;
+    nbody_force_walk<4, kGuard>(h, p, block_list(h, p.cls), tile, red);
 }
 
 // ---- each pair once --------------------------------------------------------
@@ -128,6 +135,12 @@ __global__ __launch_bounds__(256) void k_nbody_force(HeapView h, NbodyK p)
 // g + k what they took from their k-th segment.  Pairs inside a group are
 // evaluated in both orders.  Nothing is summed by atomics: the result does
 // not depend on the schedule.
+//
+// A launch holds for every list that it may find: a captured one finds, at a
+// replay, the list of a class that has grown since.  As long as the list fits
+// the rows of `part` (whole groups, so up to W / 2 - 1 blocks more than the
+// host's bound) the launch's segments cover it; beyond, the same work-groups
+// walk all pairs as k_nbody_force does, and k_nbody_sum only moves the bodies.
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 constexpr uint32_t kPairChunk = 128;
@@ -158,7 +171,8 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(4, 4))) 
 {
     constexpr uint32_t I = 32 * W;
     __shared__ float s_x[2][kPairChunk], s_y[2][kPairChunk], s_m[2][kPairChunk];
-    __shared__ float2 s_a[2][W][kPairChunk];
+    __shared__ float4 s_lds[W * kPairChunk];            // 16 bytes aligned, for the walk's tiles
+    float2 (*const s_a)[W][kPairChunk] = reinterpret_cast<float2 (*)[W][kPairChunk]>(s_lds);
     const uint32_t err = ald32(h.ctrl + CTRL_ERR);
     const BlockList L = block_list(h, p.cls);
     const uint32_t n = 64 * L.r;
@@ -170,11 +184,13 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(4, 4))) 
     while (seg * (seg + 1) / 2 > q) --seg;
     while ((seg + 1) * (seg + 2) / 2 <= q) ++seg;
     const uint32_t a = blockIdx.x - per * (seg * (seg + 1) / 2), i0 = a * I;
-    if (n > pl.stride) {                                // more blocks than the host's bound: never
-        if (threadIdx.x == 0) raise_error(h, ERR_INTERNAL);
+    if (err) return;
+    if (n > pl.stride) {                                // a class that has grown since the capture
+        nbody_force_walk<W, kGuard>(h, p, L, reinterpret_cast<float4 (*)[64]>(s_lds),
+                                    reinterpret_cast<float2 (*)[64]>(s_lds + 64 * W));
         return;
     }
-    if (err || i0 >= n || seg * pl.J >= n) return;
+    if (i0 >= n || seg * pl.J >= n) return;
     const uint32_t lane = lane_id(), w = threadIdx.x >> 6, col = lane & 31, hi = lane >> 5;
     const uint32_t ib = i0 + 32 * w;
     // this wavefront's bodies: the matrix operands, and the masses by row
@@ -290,67 +306,79 @@ __device__ __forceinline__ void nbody_move(float dt, float fx, float fy, float m
 // Adds up each body's partial sums with Kahan compensation and stores its
 // force: a work-group per listed block, whose four wavefronts take a quarter
 // of the slots each, in order, eight rows in flight (one wavefront a block
-// took 25 us over the 128 rows of 65,536 bodies: too few loads in flight).
-// kMove: also Body::update of the body, which no other work-group of the
-// launch reads.  A step of a few thousand bodies is three launches near the
-// launch floor (3,001 bodies: 9.0, 3.3 and 3.3 us and the gaps between them);
-// this one saves the third: eight steps and their read-back 273 us with it and
-// 247 without.
+// took 25 us over the 64 to 256 rows of 65,536 bodies: too few loads in
+// flight).  kMove: also Body::update of the body, which no other work-group of
+// the launch reads.  A step of a few thousand bodies is three launches near
+// the launch floor (3,001 bodies: 9.0, 3.3 and 3.3 us and the gaps between
+// them); this one saves the third: eight steps and their read-back 273 us with
+// it and 247 without.
 template <int W, bool kMove>
 __global__ __launch_bounds__(256) void k_nbody_sum(HeapView h, NbodyK p, PairPlan pl)
 {
     __shared__ float2 red[4][64];
     const uint32_t err = ald32(h.ctrl + CTRL_ERR);
     const BlockList L = block_list(h, p.cls);
-    const uint32_t e = blockIdx.x, s = lane_id(), w = threadIdx.x >> 6;
-    if (err || e >= L.r || 64 * L.r > pl.stride) return;
-    const uint32_t n = 64 * L.r, g = e * 64 / (32 * W), i = e * 64 + s;
-    const uint32_t slots = g + (n + pl.J - 1) / pl.J - g * (32 * W) / pl.J;
-    const uint32_t lo = slots * w / 4, hi = slots * (w + 1) / 4;
-    const uint32_t bid = L.at(e);
-    const uint32_t t = h.type[bid];
-    const uint64_t bm = h.alloc_bm[bid];
-    const float m = farr<float>(h, bid, p.o_m)[s];
-    float vx = 0.f, vy = 0.f, x = 0.f, y = 0.f;
-    if (kMove && w == 0) {
-        vx = farr<float>(h, bid, p.o_vx)[s];
-        vy = farr<float>(h, bid, p.o_vy)[s];
-        x = farr<float>(h, bid, p.o_x)[s];
-        y = farr<float>(h, bid, p.o_y)[s];
-    }
-    float ax = 0.f, ay = 0.f, cx = 0.f, cy = 0.f;
-    for (uint32_t k = lo; k < hi; k += 8) {
-        float2 v[8];
-#pragma unroll
-        for (uint32_t u = 0; u < 8; ++u)
-            v[u] = k + u < hi ? pl.part[(uint64_t)(k + u) * pl.stride + i] : make_float2(0.f, 0.f);
-#pragma unroll
-        for (uint32_t u = 0; u < 8; ++u) {
-            const float yx = v[u].x - cx, tx = ax + yx;
-            cx = (tx - ax) - yx;
-            ax = tx;
-            const float yy = v[u].y - cy, ty = ay + yy;
-            cy = (ty - ay) - yy;
-            ay = ty;
+    const uint32_t s = lane_id(), w = threadIdx.x >> 6, n = 64 * L.r;
+    const bool summed = n <= pl.stride;                 // else k_nbody_pairs has stored the forces
+    if (err || (!summed && !kMove)) return;
+    for (uint32_t e = blockIdx.x; e < L.r; e += gridDim.x) {
+        const uint32_t bid = L.at(e);
+        const uint32_t t = h.type[bid];
+        const uint64_t bm = h.alloc_bm[bid];
+        const float m = farr<float>(h, bid, p.o_m)[s];
+        float vx = 0.f, vy = 0.f, x = 0.f, y = 0.f, fx, fy;
+        if (kMove && w == 0) {
+            vx = farr<float>(h, bid, p.o_vx)[s];
+            vy = farr<float>(h, bid, p.o_vy)[s];
+            x = farr<float>(h, bid, p.o_x)[s];
+            y = farr<float>(h, bid, p.o_y)[s];
         }
-    }
-    red[w][s] = make_float2(ax, ay);
-    __syncthreads();
-    if (w || t != p.cls || !((bm >> s) & 1)) return;
+        if (summed) {
+            const uint32_t g = e * 64 / (32 * W), i = e * 64 + s;
+            const uint32_t slots = g + (n + pl.J - 1) / pl.J - g * (32 * W) / pl.J;
+            const uint32_t lo = slots * w / 4, hi = slots * (w + 1) / 4;
+            float ax = 0.f, ay = 0.f, cx = 0.f, cy = 0.f;
+            for (uint32_t k = lo; k < hi; k += 8) {
+                float2 v[8];
 #pragma unroll
-    for (int k = 1; k < 4; ++k) {
-        ax += red[k][s].x;
-        ay += red[k][s].y;
+                for (uint32_t u = 0; u < 8; ++u)
+                    v[u] = k + u < hi ? pl.part[(uint64_t)(k + u) * pl.stride + i] : make_float2(0.f, 0.f);
+#pragma unroll
+                for (uint32_t u = 0; u < 8; ++u) {
+                    const float yx = v[u].x - cx, tx = ax + yx;
+                    cx = (tx - ax) - yx;
+                    ax = tx;
+                    const float yy = v[u].y - cy, ty = ay + yy;
+                    cy = (ty - ay) - yy;
+                    ay = ty;
+                }
+            }
+            if (e != blockIdx.x) __syncthreads();       // the sums of the block before have been read
+            red[w][s] = make_float2(ax, ay);
+            __syncthreads();
+            if (w || t != p.cls || !((bm >> s) & 1)) continue;
+#pragma unroll
+            for (int k = 1; k < 4; ++k) {
+                ax += red[k][s].x;
+                ay += red[k][s].y;
+            }
+            const float gm = p.G * m;
+            fx = gm * ax;
+            fy = gm * ay;
+            farr<float>(h, bid, p.o_fx)[s] = fx;
+            farr<float>(h, bid, p.o_fy)[s] = fy;
+        } else {
+            if (w || t != p.cls || !((bm >> s) & 1)) continue;
+            fx = farr<float>(h, bid, p.o_fx)[s];
+            fy = farr<float>(h, bid, p.o_fy)[s];
+        }
+        if (!kMove) continue;
+        nbody_move(p.dt, fx, fy, m, vx, vy, x, y);
+        farr<float>(h, bid, p.o_vx)[s] = vx;
+        farr<float>(h, bid, p.o_vy)[s] = vy;
+        farr<float>(h, bid, p.o_x)[s] = x;
+        farr<float>(h, bid, p.o_y)[s] = y;
     }
-    const float gm = p.G * m, fx = gm * ax, fy = gm * ay;
-    farr<float>(h, bid, p.o_fx)[s] = fx;
-    farr<float>(h, bid, p.o_fy)[s] = fy;
-    if (!kMove) return;
-    nbody_move(p.dt, fx, fy, m, vx, vy, x, y);
-    farr<float>(h, bid, p.o_vx)[s] = vx;
-    farr<float>(h, bid, p.o_vy)[s] = vy;
-    farr<float>(h, bid, p.o_x)[s] = x;
-    farr<float>(h, bid, p.o_y)[s] = y;
 }
 
 // Body::update
