@@ -973,16 +973,21 @@ LaunchShape method_shape(const smmo_heap *h, uint32_t cls, uint32_t def_group, u
     return ls;
 }
 
+bool stream_captured(hipStream_t st)
+{
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &cap) != hipSuccess) {
+        (void)hipGetLastError();
+        return true;           // (the null stream while another one is captured)
+    }
+    return cap != hipStreamCaptureStatusNone;
+}
+
 void *class_workspace(smmo_heap *h, uint32_t cls, size_t bytes, hipStream_t st)
 {
     smmo_heap::Workspace *&cur = h->work[cls];
     if (cur && cur->bytes >= bytes) return cur->p;
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(st, &cap) != hipSuccess) {
-        (void)hipGetLastError();
-        return nullptr;
-    }
-    if (cap != hipStreamCaptureStatusNone) return nullptr;
+    if (stream_captured(st)) return nullptr;
     smmo_heap::Workspace *w = new (std::nothrow) smmo_heap::Workspace();
     if (!w) return nullptr;
     // room to grow by half, so that a growing class does not take one each time

@@ -157,6 +157,9 @@ bool packing_wanted(const smmo_heap *h, uint32_t cls, const LaunchShape &ls);
 // a method's device allocation, not a host-side bulk creation)
 void note_allocation(smmo_heap *h, uint32_t cls, uint64_t max_new_objects, hipStream_t st, bool in_method = true);
 
+// whether launches on the stream are being captured (not run)
+bool stream_captured(hipStream_t st);
+
 // A device workspace of at least `bytes` for a method over class cls, kept by
 // the heap (its contents do not survive a launch; classes have their own, so
 // launches over different classes may overlap).  NULL when there is none to be

@@ -155,7 +155,7 @@ __global__ __launch_bounds__(1024) void k_spring_force4(HeapView h, SpringK p)
 // node is endpoint a, -f if b), then v += F/m dt, x += v dt.  U blocks at
 // once, as in the force kernel.
 template <int U, bool NT>
-__global__ __launch_bounds__(1024) void k_spring_node(HeapView h, SpringK p)
+__device__ __forceinline__ void spring_node(const HeapView &h, const SpringK &p)
 {
     const uint32_t s = lane_id();
     for_each_block_heads<U>(h, p.node_cls, p.wpg, [&](const BlockHeads<U> &hd) {
@@ -216,6 +216,12 @@ __global__ __launch_bounds__(1024) void k_spring_node(HeapView h, SpringK p)
     });
 }
 
+template <int U, bool NT>
+__global__ __launch_bounds__(1024) void k_spring_node(HeapView h, SpringK p)
+{
+    spring_node<U, NT>(h, p);
+}
+
 // ---- several steps of a small mesh in one launch ----------------------------
 // A mesh of a few dozen blocks spends its step on two launches and their
 // chains of dependent loads (7.0 us for 957 nodes and 2,748 springs, of which
@@ -231,11 +237,14 @@ __global__ __launch_bounds__(1024) void k_spring_node(HeapView h, SpringK p)
 // last step, which leaves the heap as the separate launches do.  A handle that
 // names a block outside the two lists (a node or spring of another class with
 // the same field offsets) is followed in memory at every step.
+// A replay of a captured launch may find lists that have grown beyond the
+// registers since: a second launch, captured with it, then walks the two
+// do-alls' passes (in this kernel they would take its scalar registers).
 constexpr uint32_t kStepsMaxBlocks = 4096;   // heap blocks: the table of list positions
 constexpr uint32_t kNone16 = 0x7FFF, kFar16 = 0x7FFE;
 
 template <int SBW, int NBW>
-__global__ __launch_bounds__(1024) void k_spring_steps(HeapView h, SpringK p, uint32_t steps)
+__global__ __launch_bounds__(1024) void k_spring_steps(HeapView h, SpringK p, uint32_t steps, bool captured)
 {
     __shared__ float2 s_x[NBW * 1024], s_f[SBW * 1024];
     __shared__ uint16_t s_pos[kStepsMaxBlocks];   // list position of a block; springs' with bit 15
@@ -243,8 +252,8 @@ __global__ __launch_bounds__(1024) void k_spring_steps(HeapView h, SpringK p, ui
     const uint32_t err = ald32(h.ctrl + CTRL_ERR);
     const BlockList SL = block_list(h, p.spring_cls), NL = block_list(h, p.node_cls);
     if (err) return;
-    if (SL.r > 16 * SBW || NL.r > 16 * NBW || h.M > kStepsMaxBlocks) {   // beyond the host's bounds: never
-        if (threadIdx.x == 0) raise_error(h, ERR_INTERNAL);
+    if (SL.r > 16 * SBW || NL.r > 16 * NBW) {      // only a replay finds more than the host's bounds
+        if (!captured && threadIdx.x == 0) raise_error(h, ERR_INTERNAL);
         return;
     }
     for (uint32_t b = threadIdx.x; b < h.M; b += 1024) s_pos[b] = (uint16_t)kNone16;
@@ -393,6 +402,30 @@ __global__ __launch_bounds__(1024) void k_spring_steps(HeapView h, SpringK p, ui
     }
 }
 
+// The steps that k_spring_steps<SBW, NBW> left because a list was too long for
+// it (nothing where it was not): one work-group, the passes of the do-alls.
+template <int SBW, int NBW>
+__global__ __launch_bounds__(1024) void k_spring_steps_grown(HeapView h, SpringK p, uint32_t steps)
+{
+    if (block_list(h, p.spring_cls).r <= 16 * SBW && block_list(h, p.node_cls).r <= 16 * NBW) return;
+    for (uint32_t t = 0; t < steps; ++t) {
+        spring_force<1, false>(h, p);
+        __threadfence();                   // slots emptied and blocks released by the other wavefronts
+        __syncthreads();
+        spring_node<1, false>(h, p);
+        __threadfence();
+        __syncthreads();
+    }
+}
+
+template <int SBW, int NBW>
+void launch_spring_steps(smmo_heap *h, SpringK k, uint32_t steps, bool captured, hipStream_t st)
+{
+    hipLaunchKernelGGL((k_spring_steps<SBW, NBW>), dim3(1), dim3(1024), 0, st, h->v, k, steps, captured);
+    k.wpg = 16;
+    if (captured) hipLaunchKernelGGL((k_spring_steps_grown<SBW, NBW>), dim3(1), dim3(1024), 0, st, h->v, k, steps);
+}
+
 // Spring::link: registers the spring in its two nodes' adjacency slots
 // (slot_a of a, slot_b of b, the latter flagged as endpoint b).  Builds a
 // mesh's topology on the device after parallel_new of nodes and springs;
@@ -534,8 +567,9 @@ smmo_status run_spring_steps(smmo_heap *h, uint32_t cls, const void *args, hipSt
         !h->replayed[a.spring_class] && !h->replayed[a.node_class]) {
         if ((s = ensure_enumerated(h, a.spring_class, false, st, false, false))) return s;
         if ((s = ensure_enumerated(h, a.node_class, false, st, false, false))) return s;
-        if (sb <= 48 && nb <= 16) hipLaunchKernelGGL((k_spring_steps<3, 1>), dim3(1), dim3(1024), 0, st, h->v, k, sa.steps);
-        else hipLaunchKernelGGL((k_spring_steps<6, 2>), dim3(1), dim3(1024), 0, st, h->v, k, sa.steps);
+        const bool captured = stream_captured(st);
+        if (sb <= 48 && nb <= 16) launch_spring_steps<3, 1>(h, k, sa.steps, captured, st);
+        else launch_spring_steps<6, 2>(h, k, sa.steps, captured, st);
         return launched("k_spring_steps");
     }
     // through the do-alls themselves, with their launch shapes and snapshots

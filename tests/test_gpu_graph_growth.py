@@ -4,9 +4,10 @@ for the lists that they find, not for those that they were captured on."""
 import numpy as np
 import pytest
 
-from inputs import nbody_init
+from inputs import nbody_init, spring_mesh
 from oracle import nbody_force_at
-from paper_1908_05845_amd.sims import NbodySim
+from paper_1908_05845_amd.sims import NbodySim, SpringSim
+from test_gpu_heap import clean
 
 pytestmark = pytest.mark.gpu
 
@@ -73,3 +74,58 @@ def test_nbody_replays_after_growth(dev, blocks, steps):
         sim.heap.sync()
         check_pass(before, sim.read(), n, G, steps)
     sim.heap.close()
+
+
+def add_mesh(sim, mesh, n0, s0):
+    """A further mesh in the heap of a SpringSim, with ids from n0 and s0 on."""
+    import torch
+
+    heap, dev = sim.heap, sim.heap.dev
+    f = lambda k: torch.from_numpy(mesh[k]).to(dev)
+    N, S = mesh["x"].size, mesh["a"].size
+    nodes = heap.new("Node", N, x=f("x"), y=f("y"), vx=f("vx"), vy=f("vy"), m=f("m"),
+                     adj=torch.full((8 * N,), -1, dtype=torch.int32, device=dev),
+                     id=torch.arange(n0, n0 + N, dtype=torch.int32, device=dev)).clone()
+    heap.new("Spring", S, a=nodes[f("a").long()], b=nodes[f("b").long()], k=f("k"), L0=f("L0"),
+             slot_a=f("slot_a").to(torch.uint8), slot_b=f("slot_b").to(torch.uint8),
+             id=torch.arange(s0, s0 + S, dtype=torch.int32, device=dev))
+    heap.do("Spring", "spring.link", sim.args)
+
+
+def by_id(heap, cname, names):
+    g = heap.gather(cname, ["id"] + names)
+    o = np.argsort(g["id"].cpu().numpy())
+    return {f: g[f].cpu().numpy()[o] for f in ["id"] + names}
+
+
+# bounds at the capture of 17 and 45 blocks (the smaller form), 32 and 89 (the larger)
+@pytest.mark.parametrize("W,H", [(33, 29), (45, 43)])
+def test_spring_steps_replays_after_growth(dev, W, H):
+    """One launch's worth of blocks at the capture, more at the replays, among
+    them springs that break: every array and the heap as the do-alls leave them."""
+    first, more = spring_mesh(W, H, seed=3, v_sigma=3.0), spring_mesh(24, 22, seed=9, v_sigma=3.0)
+    a, b = (SpringSim(first, 1e-4, 0.05, extra_blocks=200) for _ in range(2))
+    g = captured(lambda st: a.step(5, stream=st))
+    n, s = first["x"].size, first["a"].size
+    for lap in range(4):
+        if lap:
+            for sim in (a, b):
+                add_mesh(sim, more, n, s)
+            n, s = n + more["x"].size, s + more["a"].size
+        a.heap.gather("Node", ["id"])             # (the lists are built anew)
+        a.heap.gather("Spring", ["id"])
+        g.replay()
+        a.heap.sync()
+        for _ in range(5):
+            b.spring_force()
+            b.node_update()
+        for cname, names in (("Node", ["x", "y", "vx", "vy"]), ("Spring", ["fx", "fy"])):
+            ra, rb = by_id(a.heap, cname, names), by_id(b.heap, cname, names)
+            for f in ra:
+                assert np.array_equal(ra[f], rb[f]), (lap, cname, f)
+        assert a.heap.stats().free_blocks == b.heap.stats().free_blocks
+        assert a.heap.stats().device_deletes == b.heap.stats().device_deletes
+        clean(a.heap)
+    assert a.heap.stats().device_deletes > 0
+    a.heap.close()
+    b.heap.close()
