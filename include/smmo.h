@@ -41,6 +41,10 @@
  *     the class the other walks, a class that gets new objects from one is
  *     walked by the other only through a snapshot (smmo_snapshot), and
  *     the methods' reads and writes of fields do not conflict.
+ *   - Calls can be captured in a HIP graph.  A captured walk visits what is
+ *     there when the graph is replayed, objects created since the capture
+ *     included: the first walk of a class in a capture records the building
+ *     of its block list.
  *   - Device pointers are addresses in device memory of the GPU the heap is
  *     on.  The caller owns every buffer it passes and keeps it alive until the
  *     work that uses it has completed.  The heap and all of its internal

@@ -887,8 +887,10 @@ namespace {
 // The state of class cls's list as launches on stream st will find it.  A
 // launch that is being captured does not run now, and runs again with every
 // replay: an enumeration inside the capture says nothing about the list that
-// launches outside find, and of the lists that exist when the capture begins
-// only those of classes without device allocation last through the replays.
+// launches outside find, and a list that is valid when the capture begins may
+// be stale at a replay (objects created since by eager calls, by other graphs
+// or by a later launch of this one), so the first walk of a class in a capture
+// records an enumeration: about 5 us a class and replay.
 int &list_state(smmo_heap *h, uint32_t cls, hipStream_t st)
 {
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
@@ -903,8 +905,7 @@ int &list_state(smmo_heap *h, uint32_t cls, hipStream_t st)
     }
     if (h->capture != id) {
         h->capture = id;
-        for (uint32_t c = 0; c < SMMO_MAX_CLASSES; ++c)
-            h->capture_rstate[c] = h->churn[c] || h->replayed[c] ? R_DIRTY : h->rstate[c];
+        for (int &state : h->capture_rstate) state = R_DIRTY;
     }
     return h->capture_rstate[cls];
 }
