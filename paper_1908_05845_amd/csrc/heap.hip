@@ -499,7 +499,10 @@ __global__ __launch_bounds__(256) void k_destroy(HeapView h, uint32_t cls, const
         gone = aand(h.alloc_bm + bid, ~bit) & bit;
         bad |= !gone;
     }
-    if (bad) raise_error(h, ERR_BADHANDLE);
+    if (bad) {
+        raise_error(h, ERR_BADHANDLE);
+        __hip_atomic_store(h.ctrl + CTRL_DESTROY, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
     count += (uint32_t)__popcll(__ballot(gone)) * (lane == 0);
     for (int d = 1; d < 64; d <<= 1) count += (uint32_t)__shfl_xor((int)count, d);
     if (lane == 0 && count) count_events(h, EV_DELS, count);
@@ -512,8 +515,14 @@ __global__ __launch_bounds__(256) void k_destroy(HeapView h, uint32_t cls, const
 // leaves it), one with free slots active.  Nothing else runs on the heap, so
 // a container is its wavefront's own; what passes on to the next levels goes
 // through the switches that other wavefronts' containers meet there.
+// On a heap that had failed before, the first launch has done nothing and this
+// one does nothing either; an error that the first launch has raised itself
+// does not keep this one from settling what was deleted until then, and its
+// last work-group takes the mark back.
 __global__ __launch_bounds__(256) void k_destroy_settle(HeapView h, uint32_t cls, uint32_t per)
 {
+    const uint32_t err = ald32(h.ctrl + CTRL_ERR), own = ald32(h.ctrl + CTRL_DESTROY);
+    if (err && !own) return;
     const uint32_t lane = lane_id(), waves = gridDim.x * (blockDim.x >> 6);
     const uint32_t c0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)global_wave_id());
     // (every waves-th container: a class's blocks lie together)
@@ -546,6 +555,15 @@ __global__ __launch_bounds__(256) void k_destroy_settle(HeapView h, uint32_t cls
                 if (!f && h.nlev > 1) q.op[2] = BitOp{c, (uint16_t)BM_FREE, 1, 1};
             }
             run_ops_lane(h, q);
+        }
+    }
+    if (!err) return;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        uint32_t *const done = h.ctrl + CTRL_DESTROY + 1;
+        if (__hip_atomic_fetch_add(done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1) {
+            __hip_atomic_store(done, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(h.ctrl + CTRL_DESTROY, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
     }
 }

@@ -54,6 +54,8 @@ enum : uint32_t {
     CTRL_ERR = 0,
     CTRL_GATHER = 8,      // u64: gather: running output count (bits 0-31) and work-groups that
                           // have counted all their objects (32-63); zero between gathers
+    CTRL_DESTROY = 10,    // 1 while the error word's error is that of a destroy whose second launch
+                          // has not ended, and (word 11) that launch's finished work-groups
     CTRL_RPACK = 16,      // [class] u64 (words 16 + 2 class): an enumeration's running
                           // dense count (bits 0-24), sparse count (25-49) and
                           // finished work-groups (50-63); zero between enumerations

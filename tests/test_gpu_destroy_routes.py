@@ -1,0 +1,81 @@
+"""smmo_destroy on a heap that has failed already, and after an error of its own."""
+
+import numpy as np
+import pytest
+
+from paper_1908_05845_amd import smmo
+from test_gpu_heap import clean, keys_of
+
+pytestmark = pytest.mark.gpu
+
+CLASSES = {"A": [("x", "f32", 1), ("key", "i32", 1)], "B": [("key", "i32", 1), ("x", "f32", 1)]}
+
+
+def make(dev, blocks, n):
+    import torch
+
+    heap = smmo.Heap(CLASSES, blocks=blocks)
+    b = heap.new("B", 100, key=torch.arange(100, dtype=torch.int32, device=dev)).clone()
+    hd = heap.new("A", n, key=torch.arange(n, dtype=torch.int32, device=dev)).clone()
+    return heap, hd, b
+
+
+def fails(heap):
+    with pytest.raises(smmo.SmmoError) as e:
+        heap.sync()
+    assert e.value.status == smmo.SMMO_EDEVICE
+
+
+@pytest.mark.parametrize("n", [1, 64, 4000])
+def test_a_failed_heap_is_left_alone(dev, n):
+    """A block's last object is taken out of its bitmap behind the library's
+    back, so that bringing the block states in line would show: after an error
+    no destroy touches anything; once the error is cleared the next one does."""
+    import torch
+
+    heap, hd, b = make(dev, 200, 64 * 100 + 37)
+    words = heap.buf[heap.base - heap.buf.data_ptr():]
+    words = words[: words.numel() // 8 * 8].view(torch.int64)
+    at = torch.nonzero(words == (1 << 37) - 1).flatten()
+    assert at.numel() == 1                        # the last block's bitmap
+    heap.destroy("A", b[:1])
+    fails(heap)
+    words[at] = 0
+    free = heap.stats().free_blocks
+    for _ in range(2):
+        heap.destroy("A", hd[:n])
+        fails(heap)
+        st = heap.stats()
+        assert st.free_blocks == free and st.device_deletes == 0
+    smmo.smmo_clear_error(heap.h)
+    heap.destroy("A", hd[:4000])
+    heap.sync()
+    st = heap.stats()
+    assert st.device_deletes == 4000 and st.free_blocks == free + 62 + 1
+    assert np.array_equal(keys_of(heap), np.arange(4000, 6400))
+    clean(heap)
+    heap.close()
+
+
+@pytest.mark.parametrize("n", [128, 4000])
+def test_an_error_of_the_call_itself(dev, n):
+    """A bad handle among good ones: what the call has deleted before the error
+    was seen is brought in line, and only by that call."""
+    import torch
+
+    heap, hd, b = make(dev, 200, 64 * 100)
+    h = torch.cat([hd[:n], b[:1]])
+    heap.destroy("A", h)
+    fails(heap)
+    st = heap.stats()
+    assert st.live_objects[heap.cls["A"]] == 6400 - st.device_deletes
+    clean(heap)
+    heap.destroy("A", hd[n:])
+    fails(heap)
+    assert heap.stats().device_deletes == st.device_deletes
+    smmo.smmo_clear_error(heap.h)
+    heap.destroy("A", hd[n:])
+    heap.sync()
+    assert heap.stats().device_deletes == st.device_deletes + 6400 - n
+    clean(heap)
+    heap.close()
