@@ -462,6 +462,20 @@ __global__ __launch_bounds__(256) void k_new_device(HeapView h, uint32_t cls, Fi
     if (out_handles) out_handles[i] = handle;
 }
 
+// Host-initiated destroy of a few objects: one wavefront that releases them as
+// a method would, each handle checked first (a live object of the class; one
+// named twice is released once).  By one wavefront only: between the check and
+// the release of another one the block could be freed.
+__global__ __launch_bounds__(64) void k_destroy_few(HeapView h, uint32_t cls, const uint32_t *handles, uint32_t n)
+{
+    if (heap_failed(h)) return;
+    const uint32_t i = threadIdx.x, hd = i < n ? handles[i] : kNull, bid = hd >> 6;
+    const bool live = hd != kNull && bid < h.M && ald32(h.type + bid) == cls &&
+                      ((ald(h.alloc_bm + bid) >> (hd & 63)) & 1);
+    if (i < n && !live) raise_error(h, ERR_BADHANDLE);
+    wave_deallocate(h, cls, hd, live);
+}
+
 // Host-initiated destroy, first launch: frees the slots of the live objects
 // that the handles name.  No block is freed and no type changes here, so the
 // type check is a plain load and the slot's old bit tells whether the handle
@@ -508,6 +522,28 @@ __global__ __launch_bounds__(256) void k_destroy(HeapView h, uint32_t cls, const
     if (lane == 0 && count) count_events(h, EV_DELS, count);
 }
 
+// The second launch of a destroy on a heap that had failed before the call does
+// nothing, as the first one did.  An error that the first launch has raised
+// itself does not keep it from settling what was deleted until then; its last
+// work-group then takes the mark of that back (every one has read it by then).
+__device__ __forceinline__ bool destroy_begins_settling(const HeapView &h, uint32_t &err)
+{
+    const uint32_t own = ald32(h.ctrl + CTRL_DESTROY);
+    err = ald32(h.ctrl + CTRL_ERR);
+    return !err || own;
+}
+
+__device__ __forceinline__ void destroy_ends_settling(const HeapView &h, uint32_t err)
+{
+    if (!err) return;
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    uint32_t *const done = h.ctrl + CTRL_DESTROY + 1;
+    if (__hip_atomic_fetch_add(done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != gridDim.x - 1) return;
+    __hip_atomic_store(done, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(h.ctrl + CTRL_DESTROY, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 // Second launch: brings the states of the class's blocks in line with their
 // slots, a container's 64 blocks at a time, `per` containers a wavefront (a
 // lane reads one, those without blocks of the class are passed over).  A block without objects
@@ -515,14 +551,10 @@ __global__ __launch_bounds__(256) void k_destroy(HeapView h, uint32_t cls, const
 // leaves it), one with free slots active.  Nothing else runs on the heap, so
 // a container is its wavefront's own; what passes on to the next levels goes
 // through the switches that other wavefronts' containers meet there.
-// On a heap that had failed before, the first launch has done nothing and this
-// one does nothing either; an error that the first launch has raised itself
-// does not keep this one from settling what was deleted until then, and its
-// last work-group takes the mark back.
 __global__ __launch_bounds__(256) void k_destroy_settle(HeapView h, uint32_t cls, uint32_t per)
 {
-    const uint32_t err = ald32(h.ctrl + CTRL_ERR), own = ald32(h.ctrl + CTRL_DESTROY);
-    if (err && !own) return;
+    uint32_t err;
+    if (!destroy_begins_settling(h, err)) return;
     const uint32_t lane = lane_id(), waves = gridDim.x * (blockDim.x >> 6);
     const uint32_t c0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)global_wave_id());
     // (every waves-th container: a class's blocks lie together)
@@ -557,15 +589,47 @@ __global__ __launch_bounds__(256) void k_destroy_settle(HeapView h, uint32_t cls
             run_ops_lane(h, q);
         }
     }
-    if (!err) return;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        uint32_t *const done = h.ctrl + CTRL_DESTROY + 1;
-        if (__hip_atomic_fetch_add(done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1) {
-            __hip_atomic_store(done, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            __hip_atomic_store(h.ctrl + CTRL_DESTROY, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
+    destroy_ends_settling(h, err);
+}
+
+// The second launch for handles that are few beside the class's blocks: of the
+// blocks that they name alone, a lane a handle (the first of those that follow
+// one another in a block).  Several lanes may still name one block: the one whose exchange unsets an empty block's type
+// frees it, and the one whose OR sets a block's active bit passes that on.
+// Activations come before the frees of any lane, so that a wavefront's
+// switches wait for none of its own that is still to come.
+// Bound by its chain of atomics, 5 to 8 of them, whatever the class's size.
+__global__ __launch_bounds__(256) void k_destroy_settle_named(HeapView h, uint32_t cls, const uint32_t *handles,
+                                                              uint32_t n)
+{
+    uint32_t err;
+    if (!destroy_begins_settling(h, err)) return;
+    const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const uint32_t hd = i < n ? handles[i] : kNull, bid = hd >> 6, c = bid >> 6;
+    const uint64_t bit = 1ull << (bid & 63);
+    const uint32_t before = (uint32_t)__shfl_up((int)bid, 1);
+    const bool up = h.nlev > 1, again = lane_id() != 0 && bid == before;
+    const bool named = hd != kNull && !again && bid < h.M && ald32(h.type + bid) == cls;
+    const uint64_t slots = named ? ald(h.alloc_bm + bid) : ~0ull;
+    bool freed = false;
+    if (slots == 0) {
+        uint32_t t = cls;
+        freed = __hip_atomic_compare_exchange_strong(h.type + bid, &t, kNull, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                     __HIP_MEMORY_SCOPE_AGENT);
     }
+    const bool some = slots != 0 && slots != ~0ull;
+    uint64_t prev = some ? aor(h.bm_word(bm_active(cls), 0, c), bit) : ~0ull;
+    switch_bits(h, up && prev == 0, bm_active(cls), c, +1, 1);
+    if (freed) {
+        __hip_atomic_store(h.alloc_bm + bid, ~0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        prev = aand(h.bm_word(bm_active(cls), 0, c), ~bit);
+    }
+    switch_bits(h, up && freed && prev == bit, bm_active(cls), c, -1, 1);
+    if (freed) prev = aand(h.bm_word(bm_alloc(cls), 0, c), ~bit);
+    switch_bits(h, up && freed && prev == bit, bm_alloc(cls), c, -1, 1);
+    if (freed) prev = aor(h.bm_word(BM_FREE, 0, c), bit);
+    switch_bits(h, up && freed && prev == 0, BM_FREE, c, +1, 1);
+    destroy_ends_settling(h, err);
 }
 
 // One run of a block's 64 slots that a gather copies: a field array of 1- or
@@ -1455,6 +1519,21 @@ smmo_status smmo_set_launch(smmo_heap *h, uint32_t method_id, uint32_t class_id,
     return SMMO_OK;
 }
 
+namespace {
+// The routes of a destroy (us; handles of consecutive objects, of random ones).
+// Up to 16 handles one launch is the faster: 7.6, 9.1 in a class of 1,600
+// blocks against 9.4, 9.8 with the settling launch; 24 handles 7.9, 10.1
+// against 9.5, 9.9.  The settling launch of the whole class reads 8 bytes a
+// block, which begins to show at half a million of them; that of the named
+// blocks costs by the handle.  160,000 blocks, 256 handles: 10.5, 12.1 and 11.2,
+// 12.3; 800,000 blocks, 16,384: 13.5, 23.6 and 13.6, 16.5, and 65,536: 13.5,
+// 31.1 and 17.1, 21.6; 16M blocks, 1,024: 51.4, 48.8 and 12.4, 13.6, and 262,144:
+// 54.5, 101 and 24.1, 51.3.
+constexpr uint32_t kDestroyFew = 16;
+constexpr uint64_t kDestroyManyBlocks = 1u << 19, kDestroyBlocksPerHandle = 32;
+static_assert(kDestroyFew <= 64, "k_destroy_few is one wavefront");
+} // namespace
+
 smmo_status smmo_destroy(smmo_heap *h, uint32_t class_id, const uint32_t *handles, uint32_t n,
                          smmo_stream stream)
 {
@@ -1464,14 +1543,24 @@ smmo_status smmo_destroy(smmo_heap *h, uint32_t class_id, const uint32_t *handle
     if (!handles) return fail(SMMO_EINVAL, "handles is NULL");
     hipStream_t st = static_cast<hipStream_t>(stream);
     h->snap_pending &= ~(1u << class_id);   // a snapshot would still list the deleted objects
+    if (n <= kDestroyFew) {
+        hipLaunchKernelGGL(k_destroy_few, dim3(1), dim3(64), 0, st, h->v, class_id, handles, n);
+        if ((s = launch_check("k_destroy_few"))) return s;
+        h->last = st;
+        return SMMO_OK;
+    }
     const uint32_t grid = (uint32_t)(((uint64_t)n + 255) / 256);
     hipLaunchKernelGGL(k_destroy, dim3(grid), dim3(256), 0, st, h->v, class_id, handles, n);
     if ((s = launch_check("k_destroy"))) return s;
-    // a container a wavefront as long as 8,192 wavefronts do
-    const uint32_t per = (h->v.lvl_n[0] + 8191) / 8192;
-    static_assert((kMaxBlocks / 64 + 1 + 8191) / 8192 <= 64, "a wavefront's containers must fit its lanes");
-    hipLaunchKernelGGL(k_destroy_settle, dim3((h->v.lvl_n[0] + 4 * per - 1) / (4 * per)), dim3(256), 0, st, h->v,
-                       class_id, per);
+    if (h->ub_blocks[class_id] >= kDestroyManyBlocks && n <= h->ub_blocks[class_id] / kDestroyBlocksPerHandle) {
+        hipLaunchKernelGGL(k_destroy_settle_named, dim3(grid), dim3(256), 0, st, h->v, class_id, handles, n);
+    } else {
+        // a container a wavefront as long as 8,192 wavefronts do
+        const uint32_t per = (h->v.lvl_n[0] + 8191) / 8192;
+        static_assert((kMaxBlocks / 64 + 1 + 8191) / 8192 <= 64, "a wavefront's containers must fit its lanes");
+        hipLaunchKernelGGL(k_destroy_settle, dim3((h->v.lvl_n[0] + 4 * per - 1) / (4 * per)), dim3(256), 0, st, h->v,
+                           class_id, per);
+    }
     if ((s = launch_check("k_destroy_settle"))) return s;
     h->last = st;
     return SMMO_OK;

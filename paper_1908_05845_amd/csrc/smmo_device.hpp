@@ -492,12 +492,12 @@ __device__ __forceinline__ void give_back_slots(const HeapView &h, uint32_t who,
     }
 }
 
-// One switch a lane, where todo, completed by all of them together (converged;
-// the lanes' switches go the same way in bitmaps of one kind, so none of them
-// waits for another one of these).
-__device__ __forceinline__ void switch_bits(const HeapView &h, bool todo, uint32_t bmid, uint32_t pos, int dir)
+// One switch a lane, where todo, beginning at level lvl, completed by all of
+// them together (converged; the lanes' switches go the same way in bitmaps of
+// one kind, so none of them waits for another one of these).
+__device__ __forceinline__ void switch_bits(const HeapView &h, bool todo, uint32_t bmid, uint32_t pos, int dir,
+                                            uint32_t lvl = 0)
 {
-    uint32_t lvl = 0;
     for (uint32_t it = 0;; ++it) {
         if (todo) {
             uint64_t *const w = h.bm_word(bmid, lvl, pos >> 6);
