@@ -362,17 +362,20 @@ __device__ __forceinline__ uint32_t pick_bit(const HeapView &h, uint64_t c, uint
 // heap, a few of them in every container, they drew as many requests as the
 // full containers did: 4096 x 4096 cells took 2.5 ms a generation (3.3 M of
 // 10.2 M searches wasted over twelve), 0.74 ms now (0.3 M of 4.2 M); 256 x 256
-// cells 29 us before both changes, 21.5 us now.
+// cells 29 us before both changes, 21.5 us now.  A search that follows a miss
+// draws there too (anywhere): the lowest window's bits may be behind, cleared
+// by a claimer that has yet to pass it on, while the other windows have blocks.
 // Converged call, every argument and the result wave-uniform.
-__device__ __forceinline__ uint32_t find_set(const HeapView &h, uint32_t who, uint32_t bmid, uint32_t seed)
+__device__ __forceinline__ uint32_t find_set(const HeapView &h, uint32_t who, uint32_t bmid, uint32_t seed,
+                                             bool anywhere = false)
 {
     count_event_one(h, who, EV_FIND);
     uint32_t idx = 0;
     for (int lvl = (int)h.nlev - 1; lvl >= 0; --lvl) {
         const uint64_t c = uniform64(ald(h.bm_word(bmid, (uint32_t)lvl, idx)));
         if (!c) return kNoBlock;
-        const uint32_t b = bmid == BM_FREE && lvl >= 2 ? (uint32_t)(__ffsll((unsigned long long)c) - 1)
-                                                       : pick_bit(h, c, seed, (uint32_t)lvl);
+        const uint32_t b = bmid == BM_FREE && lvl >= 2 && !anywhere ? (uint32_t)(__ffsll((unsigned long long)c) - 1)
+                                                                    : pick_bit(h, c, seed, (uint32_t)lvl);
         idx = idx * 64u + b;
     }
     return idx;
@@ -386,7 +389,7 @@ __device__ __forceinline__ uint32_t claim_free_block(const HeapView &h, uint32_t
 {
     uint32_t misses = 0;
     for (uint32_t t = 0; t < h.spin_limit; ++t) {
-        const uint32_t b = find_set(h, who, BM_FREE, seed + t * 0x632BE5ABu);
+        const uint32_t b = find_set(h, who, BM_FREE, seed + t * 0x632BE5ABu, misses != 0);
         if (b == kNoBlock) {
             // A search can miss while another thread is between two levels
             // of the hierarchy; only a run of consecutive misses means the
