@@ -362,9 +362,7 @@ __device__ __forceinline__ uint32_t pick_bit(const HeapView &h, uint64_t c, uint
 // heap, a few of them in every container, they drew as many requests as the
 // full containers did: 4096 x 4096 cells took 2.5 ms a generation (3.3 M of
 // 10.2 M searches wasted over twelve), 0.74 ms now (0.3 M of 4.2 M); 256 x 256
-// cells 29 us before both changes, 21.5 us now.  A search that follows a miss
-// draws there too (anywhere): the lowest window's bits may be behind, cleared
-// by a claimer that has yet to pass it on, while the other windows have blocks.
+// cells 29 us before both changes, 21.5 us now.  `anywhere` draws there too.
 // Converged call, every argument and the result wave-uniform.
 __device__ __forceinline__ uint32_t find_set(const HeapView &h, uint32_t who, uint32_t bmid, uint32_t seed,
                                              bool anywhere = false)
@@ -387,15 +385,23 @@ __device__ __forceinline__ uint32_t find_set(const HeapView &h, uint32_t who, ui
 // Converged call, wave-uniform as find_set.
 __device__ __forceinline__ uint32_t claim_free_block(const HeapView &h, uint32_t who, uint32_t seed)
 {
+    // Misses at the lowest window before the search draws at every level, and
+    // misses in a row after that which mean that the heap is exhausted: the
+    // window's summary bits may be behind, cleared by a claimer that has yet to
+    // pass it on, while the other windows have blocks.  Drawn from the first
+    // miss on, the claims scatter (4096 x 4096 cells, a frame of two
+    // generations 1180 us, 987 so; ten wa-tor iterations on 1024 x 1024 cells
+    // 4289 and 3432).
+    constexpr uint32_t kWindowMisses = 64, kDrawnMisses = 128;
     uint32_t misses = 0;
     for (uint32_t t = 0; t < h.spin_limit; ++t) {
-        const uint32_t b = find_set(h, who, BM_FREE, seed + t * 0x632BE5ABu, misses != 0);
+        const uint32_t b = find_set(h, who, BM_FREE, seed + t * 0x632BE5ABu, misses >= kWindowMisses);
         if (b == kNoBlock) {
             // A search can miss while another thread is between two levels
             // of the hierarchy; only a run of consecutive misses means the
             // heap is exhausted.  Races lost to other claimers (below) are
             // progress of others and do not count.
-            if (++misses > 128u) return kNoBlock;
+            if (++misses > kWindowMisses + kDrawnMisses) return kNoBlock;
             __builtin_amdgcn_s_sleep(4);
             continue;
         }
