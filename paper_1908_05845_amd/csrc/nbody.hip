@@ -27,14 +27,13 @@ struct NbodyK {
 
 // Body::compute_force with device_do over all bodies (Ch.7 "nbody").  A
 // work-group owns one block of 64 bodies i (one per lane in every wave);
-// its W wavefronts (four in k_nbody_force) split the other bodies j
-// block-wise (wave w takes every W-th block of R), stage each j-block in LDS
-// and read it back as broadcasts.  Each wave sums one j-block (64 terms) into
-// a fresh float32 partial and adds the partial to its running sum with Kahan
-// compensation; the W running sums are combined in wave order.  The thesis
-// leaves this shared-memory tiling as future work (its "Further
-// Optimizations").
-template <int W, bool kGuard>
+// its four wavefronts split the other bodies j block-wise (wave w takes
+// every fourth block of R), stage each j-block in LDS and read it back as
+// broadcasts.  Each wave sums one j-block (64 terms) into a fresh float32
+// partial and adds the partial to its running sum with Kahan compensation;
+// the four running sums are combined in wave order.  The thesis leaves this
+// shared-memory tiling as future work (its "Further Optimizations").
+template <bool kGuard>
 __device__ __forceinline__ void nbody_force_walk(const HeapView &h, const NbodyK &p, const BlockList &L,
                                                  float4 (*tile)[64], float2 (*red)[64])
 {
@@ -46,7 +45,7 @@ __device__ __forceinline__ void nbody_force_walk(const HeapView &h, const NbodyK
         const float xi = farr<float>(h, bid, p.o_x)[lane];
         const float yi = farr<float>(h, bid, p.o_y)[lane];
         float ax = 0.f, ay = 0.f, cx = 0.f, cy = 0.f;
-        for (uint32_t j0 = 0; j0 < L.r; j0 += W) {
+        for (uint32_t j0 = 0; j0 < L.r; j0 += 4) {
             const uint32_t jt = j0 + w;
             if (jt >= L.r) break;                        // wave-uniform
             const uint32_t jb = __builtin_amdgcn_readfirstlane(L.at(jt));
@@ -87,7 +86,7 @@ __device__ __forceinline__ void nbody_force_walk(const HeapView &h, const NbodyK
         if (w == 0 && ((bmi >> lane) & 1)) {
             float sx = 0.f, sy = 0.f;
 #pragma unroll
-            for (int k = 0; k < W; ++k) {
+            for (int k = 0; k < 4; ++k) {
                 sx += red[k][lane].x;
                 sy += red[k][lane].y;
             }
@@ -105,7 +104,7 @@ __global__ __launch_bounds__(256) void k_nbody_force(HeapView h, NbodyK p)
     __shared__ float4 tile[4][64];
     __shared__ float2 red[4][64];
     if (heap_failed(h)) return;
-    nbody_force_walk<4, kGuard>(h, p, block_list(h, p.cls), tile, red);
+    nbody_force_walk<kGuard>(h, p, block_list(h, p.cls), tile, red);
 }
 
 // ---- each pair once --------------------------------------------------------
@@ -136,11 +135,12 @@ __global__ __launch_bounds__(256) void k_nbody_force(HeapView h, NbodyK p)
 // evaluated in both orders.  Nothing is summed by atomics: the result does
 // not depend on the schedule.
 //
-// A launch holds for every list that it may find: a captured one finds, at a
-// replay, the list of a class that has grown since.  As long as the list fits
-// the rows of `part` (whole groups, so up to W / 2 - 1 blocks more than the
-// host's bound) the launch's segments cover it; beyond, the same work-groups
-// walk all pairs as k_nbody_force does, and k_nbody_sum only moves the bodies.
+// A captured launch finds, at a replay, the list of a class that may have grown
+// since.  As long as the list fits the rows of `part` (whole groups, so up to
+// W / 2 - 1 blocks more than the host's bound), the launch's segments and the
+// work-groups of k_nbody_sum cover it; beyond, the captured k_nbody_sum walks
+// all pairs as k_nbody_force does (kCaptured; the kernels of launches that are
+// not captured do without the walk and its registers).
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 constexpr uint32_t kPairChunk = 128;
@@ -164,15 +164,14 @@ __device__ __forceinline__ float3 pair_body(const HeapView &h, const NbodyK &p, 
     return t == p.cls && ((bm >> l) & 1) ? v : b;
 }
 
-template <int W, bool kGuard>
+template <int W, bool kGuard, bool kCaptured>
 __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_nbody_pairs(HeapView h,
                                                                                                   NbodyK p,
                                                                                                   PairPlan pl)
 {
     constexpr uint32_t I = 32 * W;
     __shared__ float s_x[2][kPairChunk], s_y[2][kPairChunk], s_m[2][kPairChunk];
-    __shared__ float4 s_lds[W * kPairChunk];            // 16 bytes aligned, for the walk's tiles
-    float2 (*const s_a)[W][kPairChunk] = reinterpret_cast<float2 (*)[W][kPairChunk]>(s_lds);
+    __shared__ float2 s_a[2][W][kPairChunk];
     const uint32_t err = ald32(h.ctrl + CTRL_ERR);
     const BlockList L = block_list(h, p.cls);
     const uint32_t n = 64 * L.r;
@@ -184,13 +183,11 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(4, 4))) 
     while (seg * (seg + 1) / 2 > q) --seg;
     while ((seg + 1) * (seg + 2) / 2 <= q) ++seg;
     const uint32_t a = blockIdx.x - per * (seg * (seg + 1) / 2), i0 = a * I;
-    if (err) return;
-    if (n > pl.stride) {                                // a class that has grown since the capture
-        nbody_force_walk<W, kGuard>(h, p, L, reinterpret_cast<float4 (*)[64]>(s_lds),
-                                    reinterpret_cast<float2 (*)[64]>(s_lds + 64 * W));
+    if (n > pl.stride) {                                // only a replay finds more than the host's bound
+        if (!kCaptured && threadIdx.x == 0) raise_error(h, ERR_INTERNAL);
         return;
     }
-    if (i0 >= n || seg * pl.J >= n) return;
+    if (err || i0 >= n || seg * pl.J >= n) return;
     const uint32_t lane = lane_id(), w = threadIdx.x >> 6, col = lane & 31, hi = lane >> 5;
     const uint32_t ib = i0 + 32 * w;
     // this wavefront's bodies: the matrix operands, and the masses by row
@@ -307,78 +304,76 @@ __device__ __forceinline__ void nbody_move(float dt, float fx, float fy, float m
 // force: a work-group per listed block, whose four wavefronts take a quarter
 // of the slots each, in order, eight rows in flight (one wavefront a block
 // took 25 us over the 64 to 256 rows of 65,536 bodies: too few loads in
-// flight).  kMove: also Body::update of the body, which no other work-group of
-// the launch reads.  A step of a few thousand bodies is three launches near
-// the launch floor (3,001 bodies: 9.0, 3.3 and 3.3 us and the gaps between
-// them); this one saves the third: eight steps and their read-back 273 us with
-// it and 247 without.
-template <int W, bool kMove>
+// flight).  kCaptured: also the forces of a list that is too long for the rows.
+// kMove: also Body::update of the body, which no other work-group of the
+// launch reads.  A step of a few thousand bodies is three launches near the
+// launch floor (3,001 bodies: 9.0, 3.3 and 3.3 us and the gaps between them);
+// this one saves the third: eight steps and their read-back 273 us with it and
+// 247 without.
+template <int W, bool kMove, bool kCaptured>
 __global__ __launch_bounds__(256) void k_nbody_sum(HeapView h, NbodyK p, PairPlan pl)
 {
+    static_assert(!(kMove && kCaptured), "the walk reads positions that other work-groups would move");
     __shared__ float2 red[4][64];
     const uint32_t err = ald32(h.ctrl + CTRL_ERR);
     const BlockList L = block_list(h, p.cls);
-    const uint32_t s = lane_id(), w = threadIdx.x >> 6, n = 64 * L.r;
-    const bool summed = n <= pl.stride;                 // else k_nbody_pairs has stored the forces
-    if (err || (!summed && !kMove)) return;
-    for (uint32_t e = blockIdx.x; e < L.r; e += gridDim.x) {
-        const uint32_t bid = L.at(e);
-        const uint32_t t = h.type[bid];
-        const uint64_t bm = h.alloc_bm[bid];
-        const float m = farr<float>(h, bid, p.o_m)[s];
-        float vx = 0.f, vy = 0.f, x = 0.f, y = 0.f, fx, fy;
-        if (kMove && w == 0) {
-            vx = farr<float>(h, bid, p.o_vx)[s];
-            vy = farr<float>(h, bid, p.o_vy)[s];
-            x = farr<float>(h, bid, p.o_x)[s];
-            y = farr<float>(h, bid, p.o_y)[s];
+    const uint32_t e = blockIdx.x, s = lane_id(), w = threadIdx.x >> 6;
+    if constexpr (kCaptured) {
+        __shared__ float4 tile[4][64];
+        if (!err && 64 * L.r > pl.stride) {
+            if (p.eps2 > 0.f) nbody_force_walk<false>(h, p, L, tile, red);
+            else nbody_force_walk<true>(h, p, L, tile, red);
+            return;
         }
-        if (summed) {
-            const uint32_t g = e * 64 / (32 * W), i = e * 64 + s;
-            const uint32_t slots = g + (n + pl.J - 1) / pl.J - g * (32 * W) / pl.J;
-            const uint32_t lo = slots * w / 4, hi = slots * (w + 1) / 4;
-            float ax = 0.f, ay = 0.f, cx = 0.f, cy = 0.f;
-            for (uint32_t k = lo; k < hi; k += 8) {
-                float2 v[8];
-#pragma unroll
-                for (uint32_t u = 0; u < 8; ++u)
-                    v[u] = k + u < hi ? pl.part[(uint64_t)(k + u) * pl.stride + i] : make_float2(0.f, 0.f);
-#pragma unroll
-                for (uint32_t u = 0; u < 8; ++u) {
-                    const float yx = v[u].x - cx, tx = ax + yx;
-                    cx = (tx - ax) - yx;
-                    ax = tx;
-                    const float yy = v[u].y - cy, ty = ay + yy;
-                    cy = (ty - ay) - yy;
-                    ay = ty;
-                }
-            }
-            if (e != blockIdx.x) __syncthreads();       // the sums of the block before have been read
-            red[w][s] = make_float2(ax, ay);
-            __syncthreads();
-            if (w || t != p.cls || !((bm >> s) & 1)) continue;
-#pragma unroll
-            for (int k = 1; k < 4; ++k) {
-                ax += red[k][s].x;
-                ay += red[k][s].y;
-            }
-            const float gm = p.G * m;
-            fx = gm * ax;
-            fy = gm * ay;
-            farr<float>(h, bid, p.o_fx)[s] = fx;
-            farr<float>(h, bid, p.o_fy)[s] = fy;
-        } else {
-            if (w || t != p.cls || !((bm >> s) & 1)) continue;
-            fx = farr<float>(h, bid, p.o_fx)[s];
-            fy = farr<float>(h, bid, p.o_fy)[s];
-        }
-        if (!kMove) continue;
-        nbody_move(p.dt, fx, fy, m, vx, vy, x, y);
-        farr<float>(h, bid, p.o_vx)[s] = vx;
-        farr<float>(h, bid, p.o_vy)[s] = vy;
-        farr<float>(h, bid, p.o_x)[s] = x;
-        farr<float>(h, bid, p.o_y)[s] = y;
     }
+    if (err || e >= L.r || 64 * L.r > pl.stride) return;
+    const uint32_t n = 64 * L.r, g = e * 64 / (32 * W), i = e * 64 + s;
+    const uint32_t slots = g + (n + pl.J - 1) / pl.J - g * (32 * W) / pl.J;
+    const uint32_t lo = slots * w / 4, hi = slots * (w + 1) / 4;
+    const uint32_t bid = L.at(e);
+    const uint32_t t = h.type[bid];
+    const uint64_t bm = h.alloc_bm[bid];
+    const float m = farr<float>(h, bid, p.o_m)[s];
+    float vx = 0.f, vy = 0.f, x = 0.f, y = 0.f;
+    if (kMove && w == 0) {
+        vx = farr<float>(h, bid, p.o_vx)[s];
+        vy = farr<float>(h, bid, p.o_vy)[s];
+        x = farr<float>(h, bid, p.o_x)[s];
+        y = farr<float>(h, bid, p.o_y)[s];
+    }
+    float ax = 0.f, ay = 0.f, cx = 0.f, cy = 0.f;
+    for (uint32_t k = lo; k < hi; k += 8) {
+        float2 v[8];
+#pragma unroll
+        for (uint32_t u = 0; u < 8; ++u)
+            v[u] = k + u < hi ? pl.part[(uint64_t)(k + u) * pl.stride + i] : make_float2(0.f, 0.f);
+#pragma unroll
+        for (uint32_t u = 0; u < 8; ++u) {
+            const float yx = v[u].x - cx, tx = ax + yx;
+            cx = (tx - ax) - yx;
+            ax = tx;
+            const float yy = v[u].y - cy, ty = ay + yy;
+            cy = (ty - ay) - yy;
+            ay = ty;
+        }
+    }
+    red[w][s] = make_float2(ax, ay);
+    __syncthreads();
+    if (w || t != p.cls || !((bm >> s) & 1)) return;
+#pragma unroll
+    for (int k = 1; k < 4; ++k) {
+        ax += red[k][s].x;
+        ay += red[k][s].y;
+    }
+    const float gm = p.G * m, fx = gm * ax, fy = gm * ay;
+    farr<float>(h, bid, p.o_fx)[s] = fx;
+    farr<float>(h, bid, p.o_fy)[s] = fy;
+    if (!kMove) return;
+    nbody_move(p.dt, fx, fy, m, vx, vy, x, y);
+    farr<float>(h, bid, p.o_vx)[s] = vx;
+    farr<float>(h, bid, p.o_vy)[s] = vy;
+    farr<float>(h, bid, p.o_x)[s] = x;
+    farr<float>(h, bid, p.o_y)[s] = y;
 }
 
 // Body::update
@@ -449,15 +444,16 @@ uint64_t pair_rows(uint64_t slots, const PairShape &s)
     return rows;
 }
 
-template <int W>
+template <int W, bool kCaptured>
 void launch_pairs(smmo_heap *h, const NbodyK &k, const PairPlan &pl, uint64_t blocks, bool move, hipStream_t st)
 {
     const uint64_t segs = (64 * blocks + pl.J - 1) / pl.J;
     const dim3 grid((uint32_t)(pl.J / (32 * W) * (segs * (segs + 1) / 2)));
-    if (k.eps2 > 0.f) hipLaunchKernelGGL((k_nbody_pairs<W, false>), grid, dim3(64 * W), 0, st, h->v, k, pl);
-    else hipLaunchKernelGGL((k_nbody_pairs<W, true>), grid, dim3(64 * W), 0, st, h->v, k, pl);
-    if (move) hipLaunchKernelGGL((k_nbody_sum<W, true>), dim3((uint32_t)blocks), dim3(256), 0, st, h->v, k, pl);
-    else hipLaunchKernelGGL((k_nbody_sum<W, false>), dim3((uint32_t)blocks), dim3(256), 0, st, h->v, k, pl);
+    if (k.eps2 > 0.f) hipLaunchKernelGGL((k_nbody_pairs<W, false, kCaptured>), grid, dim3(64 * W), 0, st, h->v, k, pl);
+    else hipLaunchKernelGGL((k_nbody_pairs<W, true, kCaptured>), grid, dim3(64 * W), 0, st, h->v, k, pl);
+    const dim3 covered(pl.stride / 64);                 // the blocks of whole groups
+    if (move) hipLaunchKernelGGL((k_nbody_sum<W, true, false>), covered, dim3(256), 0, st, h->v, k, pl);
+    else hipLaunchKernelGGL((k_nbody_sum<W, false, kCaptured>), covered, dim3(256), 0, st, h->v, k, pl);
 }
 
 // The pair kernel's plan for class cls, whose list is ready: whether it takes
@@ -475,8 +471,13 @@ bool pair_plan(smmo_heap *h, uint32_t cls, uint64_t blocks, PairShape &sh, PairP
 void run_pairs(smmo_heap *h, const NbodyK &k, const PairShape &sh, const PairPlan &pl, uint64_t blocks, bool move,
                hipStream_t st)
 {
-    if (sh.W == 4) launch_pairs<4>(h, k, pl, blocks, move, st);
-    else launch_pairs<8>(h, k, pl, blocks, move, st);
+    if (stream_captured(st)) {                          // (never with `move`)
+        if (sh.W == 4) launch_pairs<4, true>(h, k, pl, blocks, false, st);
+        else launch_pairs<8, true>(h, k, pl, blocks, false, st);
+    } else {
+        if (sh.W == 4) launch_pairs<4, false>(h, k, pl, blocks, move, st);
+        else launch_pairs<8, false>(h, k, pl, blocks, move, st);
+    }
 }
 
 smmo_status nbody_force_launch(smmo_heap *h, uint32_t cls, const void *args, hipStream_t st)
@@ -517,8 +518,9 @@ smmo_status nbody_update_launch(smmo_heap *h, uint32_t cls, const void *args, hi
 }
 
 // nbody.steps on Body: `steps` times nbody.force and nbody.update, a body moved
-// by the launch that adds up its force where the class takes the pair form and
-// no snapshot taken ahead waits for one of the two do-alls.
+// by the launch that adds up its force where the class takes the pair form, no
+// snapshot taken ahead waits for one of the two do-alls and the launches are
+// not captured (a replay may have to walk all pairs before any body moves).
 smmo_status nbody_steps_launch(smmo_heap *h, uint32_t cls, const void *args, hipStream_t st)
 {
     smmo_nbody_steps_args sa;
@@ -532,7 +534,7 @@ smmo_status nbody_steps_launch(smmo_heap *h, uint32_t cls, const void *args, hip
     const uint64_t blocks = std::max<uint64_t>(1, h->ub_blocks[cls]);
     PairShape sh;
     PairPlan pl;
-    if (!((h->v.snap >> cls) & 1)) {
+    if (!((h->v.snap >> cls) & 1) && !stream_captured(st)) {
         if ((s = ensure_enumerated(h, cls, false, st))) return s;
         if (pair_plan(h, cls, blocks, sh, pl, st)) {
             for (uint32_t t = 0; t < sa.steps; ++t) run_pairs(h, k, sh, pl, blocks, true, st);
