@@ -49,11 +49,14 @@
  *     on.  The caller owns every buffer it passes and keeps it alive until the
  *     work that uses it has completed.  The heap and all of its internal
  *     arrays are carved out of the buffer given to smmo_alloc_heap().  The one
- *     thing that libsmmo allocates is a workspace of nbody.force's per class,
- *     on its first call on 12 to 1,536 blocks (134 MB for 65,536 bodies; from
- *     the heap's allocator callback if it has one, never under graph
- *     capture), kept until smmo_heap_free(); where there is none to be had
- *     the method takes a kernel that needs none.
+ *     thing that libsmmo allocates is a workspace per class of nbody.force and
+ *     nbody.steps, at the first call on 12 to 1,536 blocks (134 MB for 65,536
+ *     bodies; from the heap's allocator callback if it has one, never under
+ *     graph capture).  A class that outgrows it takes a larger one, 302 MB at
+ *     most, and the call waits for the class's last pass and gives the smaller
+ *     one back, unless a captured pass uses it; what is held then goes at
+ *     smmo_heap_free().  Where there is none to be had the methods take a
+ *     kernel that needs none.
  *   - Handles are 32-bit: (block index << 6) | slot.  SMMO_NULL names no
  *     object.  Handles of live objects are < 2^31, so the top bit is free for
  *     the caller to use as a flag in handle-valued fields.

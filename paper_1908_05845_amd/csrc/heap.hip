@@ -1066,32 +1066,57 @@ bool stream_captured(hipStream_t st)
     return cap != hipStreamCaptureStatusNone;
 }
 
-void *class_workspace(smmo_heap *h, uint32_t cls, size_t bytes, hipStream_t st)
+namespace {
+void release_workspace(smmo_heap *h, smmo_heap::Workspace *w)
+{
+    if (h->owner.release) h->owner.release(w->p, w->bytes, h->owner.ctx);
+    else (void)hipFree(w->p);
+    delete w;
+}
+} // namespace
+
+void *class_workspace(smmo_heap *h, uint32_t cls, size_t bytes, size_t most, hipStream_t st)
 {
     smmo_heap::Workspace *&cur = h->work[cls];
-    if (cur && cur->bytes >= bytes) return cur->p;
-    if (stream_captured(st)) return nullptr;
-    smmo_heap::Workspace *w = new (std::nothrow) smmo_heap::Workspace();
-    if (!w) return nullptr;
+    const bool captured = stream_captured(st);
+    if (cur && cur->bytes >= bytes) {
+        cur->last = st;
+        cur->captured |= captured;
+        return cur->p;
+    }
+    if (captured) return nullptr;
+    // (another stream may be captured just now, which a wait, an allocation or
+    // a release in the thread's default mode would break)
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    const bool swapped = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
     // room to grow by half, so that a growing class does not take one each time
-    w->bytes = cur ? bytes + bytes / 2 : bytes;
-    if (h->owner.alloc) {
-        w->p = h->owner.alloc(w->bytes, h->owner.ctx);
-    } else {
-        // (another stream may be captured just now, which an allocation in the
-        // thread's default mode would break)
-        hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
-        const bool swapped = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
-        if (hipMalloc(&w->p, w->bytes) != hipSuccess) {
+    const size_t want = cur ? std::min(bytes + bytes / 2, std::max(bytes, most)) : bytes;
+    if (cur && !cur->captured) {
+        if (!stream_captured(cur->last) && hipStreamSynchronize(cur->last) == hipSuccess) {
+            smmo_heap::Workspace *const older = cur->older;
+            release_workspace(h, cur);
+            cur = older;
+        } else {
+            (void)hipGetLastError();
+        }
+    }
+    smmo_heap::Workspace *w = new (std::nothrow) smmo_heap::Workspace();
+    if (w) {
+        w->bytes = want;
+        if (h->owner.alloc) {
+            w->p = h->owner.alloc(w->bytes, h->owner.ctx);
+        } else if (hipMalloc(&w->p, w->bytes) != hipSuccess) {
             (void)hipGetLastError();
             w->p = nullptr;
         }
-        if (swapped) (void)hipThreadExchangeStreamCaptureMode(&mode);
+        if (!w->p) {
+            delete w;
+            w = nullptr;
+        }
     }
-    if (!w->p) {
-        delete w;
-        return nullptr;
-    }
+    if (swapped) (void)hipThreadExchangeStreamCaptureMode(&mode);
+    if (!w) return nullptr;
+    w->last = st;
     w->older = cur;
     cur = w;
     return w->p;
@@ -1394,9 +1419,7 @@ smmo_status smmo_heap_free(smmo_heap *h)
     for (smmo_heap::Workspace *&w : h->work)
         while (w) {
             smmo_heap::Workspace *const older = w->older;
-            if (h->owner.release) h->owner.release(w->p, w->bytes, h->owner.ctx);
-            else (void)hipFree(w->p);
-            delete w;
+            release_workspace(h, w);
             w = older;
         }
     if (h->host_ctrl) (void)hipHostFree(h->host_ctrl);

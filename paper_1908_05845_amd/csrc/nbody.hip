@@ -425,9 +425,11 @@ struct PairShape {
     uint32_t W, J;
 };
 
+constexpr uint64_t kPairMostBlocks = 1536;
+
 PairShape pair_shape(uint64_t blocks)
 {
-    if (blocks < 12 || blocks > 1536) return {0, 0};
+    if (blocks < 12 || blocks > kPairMostBlocks) return {0, 0};
     if (blocks <= 96) return {4, 128};
     if (blocks <= 224) return {4, 256};
     if (blocks <= 512) return {4, 512};
@@ -456,15 +458,27 @@ void launch_pairs(smmo_heap *h, const NbodyK &k, const PairPlan &pl, uint64_t bl
     else hipLaunchKernelGGL((k_nbody_sum<W, false, kCaptured>), covered, dim3(256), 0, st, h->v, k, pl);
 }
 
+uint64_t pair_stride(uint64_t blocks, const PairShape &s)
+{
+    const uint64_t I = 32 * s.W;
+    return (64 * blocks + I - 1) / I * I;
+}
+
+uint64_t pair_bytes(uint64_t blocks)
+{
+    const PairShape s = pair_shape(blocks);
+    return pair_rows(64 * blocks, s) * pair_stride(blocks, s) * sizeof(float2);
+}
+
 // The pair kernel's plan for class cls, whose list is ready: whether it takes
 // the pair form, and then the workspace that holds the partial sums.
 bool pair_plan(smmo_heap *h, uint32_t cls, uint64_t blocks, PairShape &sh, PairPlan &pl, hipStream_t st)
 {
     sh = pair_shape(blocks);
     if (!sh.W || h->replayed[cls] || ((h->v.direct >> cls) & 1)) return false;
-    const uint64_t I = 32 * sh.W, stride = (64 * blocks + I - 1) / I * I;
-    float2 *part = static_cast<float2 *>(class_workspace(h, cls, pair_rows(64 * blocks, sh) * stride * sizeof(float2), st));
-    pl = PairPlan{part, (uint32_t)stride, sh.J};
+    static const uint64_t most = pair_bytes(kPairMostBlocks);
+    float2 *part = static_cast<float2 *>(class_workspace(h, cls, pair_bytes(blocks), most, st));
+    pl = PairPlan{part, (uint32_t)pair_stride(blocks, sh), sh.J};
     return part != nullptr;
 }
 

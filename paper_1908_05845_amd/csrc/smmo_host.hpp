@@ -95,11 +95,13 @@ struct smmo_heap {
     uint8_t launch_group[64][SMMO_MAX_CLASSES] = {};
     uint32_t cur_method = 0xFFFFFFFFu;     // method being launched by smmo_parallel_do
     // device workspaces of methods over a class (class_workspace): the one in
-    // use per class, and all that were taken, which graphs may refer to and
-    // smmo_heap_free gives back
+    // use per class, and before it those that were outgrown but that a captured
+    // launch refers to; smmo_heap_free gives them back
     struct Workspace {
         void *p = nullptr;
         size_t bytes = 0;
+        hipStream_t last = nullptr;    // of the last launch that uses it
+        bool captured = false;         // a captured launch uses it
         Workspace *older = nullptr;
     };
     Workspace *work[SMMO_MAX_CLASSES] = {};
@@ -160,12 +162,15 @@ void note_allocation(smmo_heap *h, uint32_t cls, uint64_t max_new_objects, hipSt
 // whether launches on the stream are being captured (not run)
 bool stream_captured(hipStream_t st);
 
-// A device workspace of at least `bytes` for a method over class cls, kept by
+// A device workspace of at least `bytes` (of at most `most`, what the method
+// can ever need) for launches of a method over class cls on stream st, kept by
 // the heap (its contents do not survive a launch; classes have their own, so
 // launches over different classes may overlap).  NULL when there is none to be
 // had: the method then takes a path without one.  A stream that is being
-// captured gets only a workspace that is there already.
-void *class_workspace(smmo_heap *h, uint32_t cls, size_t bytes, hipStream_t st);
+// captured gets only a workspace that is there already.  One that the class
+// has outgrown is given back once its last launch has ended (the call waits
+// for that), unless a captured launch uses it.
+void *class_workspace(smmo_heap *h, uint32_t cls, size_t bytes, size_t most, hipStream_t st);
 
 struct MethodEntry {
     const char *name;
