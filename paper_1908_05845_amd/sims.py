@@ -70,6 +70,15 @@ def _count(n):
     return max(operator.index(n), 0)
 
 
+def _counts(n):
+    """n steps as counts that fit the argument structs' 32 bits."""
+    n, most = _count(n), (1 << 32) - 1
+    while n > most:
+        yield most
+        n -= most
+    yield n
+
+
 def _repeat(heap, args, launches, n, stream):
     """n times the do-alls `launches` = [(class, method), ...] with one
     argument struct, on one stream, looked up once: a launch then costs one
@@ -344,8 +353,9 @@ class NbodySim:
 
     def step(self, n: int = 1, stream=None):
         a = self.args
-        steps = smmo.smmo_nbody_steps_args(a.G, a.eps, a.dt, _count(n))
-        smmo.smmo_parallel_do(self.heap.h, self.cls, self.m_steps, steps, stream)
+        for k in _counts(n):
+            steps = smmo.smmo_nbody_steps_args(a.G, a.eps, a.dt, k)
+            smmo.smmo_parallel_do(self.heap.h, self.cls, self.m_steps, steps, stream)
 
     def read(self):
         g = self.heap.gather("Body")
@@ -424,8 +434,9 @@ class SpringSim:
 
     def step(self, n: int = 1, stream=None):
         a = self.args
-        steps = smmo.smmo_spring_steps_args(a.node_class, a.spring_class, a.dt, a.strain_limit, a.flags, _count(n))
-        smmo.smmo_parallel_do(self.heap.h, self.heap.cls["Spring"], self.m_steps, steps, stream)
+        for k in _counts(n):
+            steps = smmo.smmo_spring_steps_args(a.node_class, a.spring_class, a.dt, a.strain_limit, a.flags, k)
+            smmo.smmo_parallel_do(self.heap.h, self.heap.cls["Spring"], self.m_steps, steps, stream)
 
     def read(self):
         """Canonical state: node arrays by node id, spring arrays by spring id
