@@ -241,6 +241,9 @@ __global__ __launch_bounds__(1024) void k_spring_node(HeapView h, SpringK p)
 // registers since: a second launch, captured with it, then walks the two
 // do-alls' passes (in this kernel they would take its scalar registers).
 constexpr uint32_t kStepsMaxBlocks = 4096;   // heap blocks: the table of list positions
+// Steps of one launch, so that it ends within 17 ms at most (4.2 us a step):
+// nothing else on the stream runs meanwhile.  A launch more costs 7 us.
+constexpr uint32_t kStepsMost = 4096;
 constexpr uint32_t kNone16 = 0x7FFF, kFar16 = 0x7FFE;
 
 template <int SBW, int NBW>
@@ -421,9 +424,12 @@ __global__ __launch_bounds__(1024) void k_spring_steps_grown(HeapView h, SpringK
 template <int SBW, int NBW>
 void launch_spring_steps(smmo_heap *h, SpringK k, uint32_t steps, bool captured, hipStream_t st)
 {
-    hipLaunchKernelGGL((k_spring_steps<SBW, NBW>), dim3(1), dim3(1024), 0, st, h->v, k, steps, captured);
     k.wpg = 16;
-    if (captured) hipLaunchKernelGGL((k_spring_steps_grown<SBW, NBW>), dim3(1), dim3(1024), 0, st, h->v, k, steps);
+    for (uint32_t left = steps, n; left; left -= n) {
+        n = std::min(left, kStepsMost);
+        hipLaunchKernelGGL((k_spring_steps<SBW, NBW>), dim3(1), dim3(1024), 0, st, h->v, k, n, captured);
+        if (captured) hipLaunchKernelGGL((k_spring_steps_grown<SBW, NBW>), dim3(1), dim3(1024), 0, st, h->v, k, n);
+    }
 }
 
 // Spring::link: registers the spring in its two nodes' adjacency slots
