@@ -177,15 +177,17 @@ struct BitOp {
     int8_t dir;
 };
 
-constexpr int kMaxOps = 6;
-
 // Invalidation attempts of one block (Alg. invalidate with rollback) before
-// the release that emptied it gives up, and the most switches one release
-// makes, which a queue holds: a re-activation, a rollback per failed attempt but the last, and
-// the three switches of a successful invalidation.
-constexpr int kInvalidateAttempts = kMaxOps - 3;
+// the release that emptied it gives up.  A further attempt follows only where
+// slots were reserved and released again between two atomics of this one.
+constexpr int kInvalidateAttempts = 3;
+
+// The most switches that one release calls for: a re-activation, a rollback
+// per failed attempt but the last, and the three of a successful invalidation.
+// Releases make each as it falls due; a queue has room for as many, and its
+// users (a destroy's settling launch and defragmentation) fill at most three.
 constexpr int kMaxReleaseOps = 1 + (kInvalidateAttempts - 1) + 3;
-static_assert(kMaxReleaseOps <= kMaxOps, "a release can queue more bitmap switches than the queue holds");
+constexpr int kMaxOps = kMaxReleaseOps;
 
 // A lane's queue of pending switches.  A push into a full queue is not
 // dropped silently: it marks the queue, and completing the queue raises
