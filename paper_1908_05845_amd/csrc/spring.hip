@@ -246,8 +246,8 @@ constexpr uint32_t kStepsMaxBlocks = 4096;   // heap blocks: the table of list p
 constexpr uint32_t kStepsMost = 4096;
 constexpr uint32_t kNone16 = 0x7FFF, kFar16 = 0x7FFE;
 
-template <int SBW, int NBW>
-__global__ __launch_bounds__(1024) void k_spring_steps(HeapView h, SpringK p, uint32_t steps, bool captured)
+template <int SBW, int NBW, bool kCaptured>
+__global__ __launch_bounds__(1024) void k_spring_steps(HeapView h, SpringK p, uint32_t steps)
 {
     __shared__ float2 s_x[NBW * 1024], s_f[SBW * 1024];
     __shared__ uint16_t s_pos[kStepsMaxBlocks];   // list position of a block; springs' with bit 15
@@ -255,8 +255,8 @@ __global__ __launch_bounds__(1024) void k_spring_steps(HeapView h, SpringK p, ui
     const uint32_t err = ald32(h.ctrl + CTRL_ERR);
     const BlockList SL = block_list(h, p.spring_cls), NL = block_list(h, p.node_cls);
     if (err) return;
-    if (SL.r > 16 * SBW || NL.r > 16 * NBW) {      // only a replay finds more than the host's bounds
-        if (!captured && threadIdx.x == 0) raise_error(h, ERR_INTERNAL);
+    if (SL.r > 16 * SBW || NL.r > 16 * NBW || h.M > kStepsMaxBlocks) {   // only a replay finds more than the host's bounds
+        if (!kCaptured && threadIdx.x == 0) raise_error(h, ERR_INTERNAL);
         return;
     }
     for (uint32_t b = threadIdx.x; b < h.M; b += 1024) s_pos[b] = (uint16_t)kNone16;
@@ -427,8 +427,12 @@ void launch_spring_steps(smmo_heap *h, SpringK k, uint32_t steps, bool captured,
     k.wpg = 16;
     for (uint32_t left = steps, n; left; left -= n) {
         n = std::min(left, kStepsMost);
-        hipLaunchKernelGGL((k_spring_steps<SBW, NBW>), dim3(1), dim3(1024), 0, st, h->v, k, n, captured);
-        if (captured) hipLaunchKernelGGL((k_spring_steps_grown<SBW, NBW>), dim3(1), dim3(1024), 0, st, h->v, k, n);
+        if (captured) {
+            hipLaunchKernelGGL((k_spring_steps<SBW, NBW, true>), dim3(1), dim3(1024), 0, st, h->v, k, n);
+            hipLaunchKernelGGL((k_spring_steps_grown<SBW, NBW>), dim3(1), dim3(1024), 0, st, h->v, k, n);
+        } else {
+            hipLaunchKernelGGL((k_spring_steps<SBW, NBW, false>), dim3(1), dim3(1024), 0, st, h->v, k, n);
+        }
     }
 }
 
