@@ -420,7 +420,9 @@ smmo_status bind_nbody(smmo_heap *h, uint32_t cls, const smmo_nbody_args &a, Nbo
 // partial sums' memory, which grows with the square of the class (134 MB for
 // 65,536 bodies), for 1-2 % of the time (32,000: W 4 J 512 219, W 8 J 1024
 // 225); past 98,000 bodies they would take over 300 MB and the class goes
-// back to k_nbody_force.
+// back to k_nbody_force.  `blocks` is the host's bound, which
+// grows with every creation and never falls: a small class whose bodies are
+// destroyed and created again drifts to the larger shapes and past the last.
 struct PairShape {
     uint32_t W, J;
 };

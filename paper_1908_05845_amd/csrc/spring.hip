@@ -560,7 +560,8 @@ smmo_status launch_spring(smmo_heap *h, uint32_t cls, const void *args, hipStrea
 // In one launch where the mesh fits one work-group's passes and no snapshot
 // taken ahead waits for one of the two do-alls.  The line lies where the
 // registers of 16 wavefronts end, at 96 and 32 blocks: one launch is still the
-// faster there (4.2 against 6.5 us a step, see k_spring_steps).
+// faster there (4.2 against 6.5 us a step, see k_spring_steps).  The blocks are
+// the host's bounds, which deletions do not lower.
 smmo_status run_spring_steps(smmo_heap *h, uint32_t cls, const void *args, hipStream_t st)
 {
     smmo_spring_steps_args sa;
