@@ -44,7 +44,8 @@
  *   - Calls can be captured in a HIP graph.  A captured walk visits what is
  *     there when the graph is replayed, objects created since the capture
  *     included: the first walk of a class in a capture records the building
- *     of its block list.
+ *     of its block list (one that uses a snapshot taken before the capture
+ *     walks that snapshot's list, as it then is).
  *   - Device pointers are addresses in device memory of the GPU the heap is
  *     on.  The caller owns every buffer it passes and keeps it alive until the
  *     work that uses it has completed.  The heap and all of its internal
